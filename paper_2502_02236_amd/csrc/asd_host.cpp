@@ -58,12 +58,13 @@ struct Layout {
     int32_t n_grains = 0;  // over all systems
     int32_t n_tiles = 0;   // plain tiles
     int32_t n_ftiles = 0;  // fused tiles
+    int32_t n_parts = 1;   // parts each grain's site list is summed in
     size_t off_S[3] = {0, 0, 0};
     size_t off_F0 = 0, off_Bt = 0;  // stash buffers of the two-pass variant 1
     size_t off_can32 = 0;
     size_t off_label = 0, off_ell = 0, off_sys = 0, off_tile = 0, off_ftile = 0, off_can = 0,
            off_ku = 0, off_gsys = 0, off_gptr = 0, off_gsites = 0, off_step = 0, off_origin = 0,
-           off_bits = 0, off_gout = 0, off_sout = 0, off_mom = 0, off_epart = 0, off_eout = 0;
+           off_bits = 0, off_gout = 0, off_rpart = 0, off_sout = 0, off_mom = 0, off_epart = 0, off_eout = 0;
     // demagnetising field (when asd_params.demag_cell is set)
     DemagDev dm{};            // geometry; pointers filled at create
     size_t off_dwx = 0, off_dwy = 0, off_dbd[2] = {0, 0}, off_dK = 0, off_dtw[3] = {0, 0, 0};
@@ -533,6 +534,13 @@ static Layout make_layout(const asd_params *p, const asd_system_desc *sys, int n
     L.off_step = take(sizeof(int64_t));
     L.off_origin = take((size_t)n_sys * sizeof(int32_t));
     L.off_bits = take(kMaxBits);
+    // parts of a grain's sum: about 2048 sites each, and no more workgroups than
+    // fill the chip a few times over
+    {
+        const int64_t G = std::max(g, 1);
+        L.n_parts = (int32_t)std::max<int64_t>(1, std::min((n / G + 2047) / 2048, 2048 / G));
+        L.off_rpart = take((size_t)G * L.n_parts * 4 * sizeof(double));
+    }
     L.off_gout = take((size_t)std::max(g, 1) * 4 * sizeof(double));
     L.off_sout = take((size_t)n_sys * 4 * sizeof(double));
     L.off_mom = take((size_t)n_sys * 5 * sizeof(double));
@@ -1242,6 +1250,8 @@ static RedArgs red_args(const asd_t *h)
     a.grain_ptr = (const int64_t *)(w + L.off_gptr);
     a.grain_sites = (const int32_t *)(w + L.off_gsites);
     a.origin = (const int32_t *)(w + L.off_origin);
+    a.part = (double *)(w + L.off_rpart);
+    a.n_parts = L.n_parts;
     a.grain_out = (double *)(w + L.off_gout);
     a.sys_out = (double *)(w + L.off_sout);
     a.moments = (double *)(w + L.off_mom);

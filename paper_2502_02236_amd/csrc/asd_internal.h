@@ -201,11 +201,13 @@ struct RedArgs {
     const int64_t *grain_ptr;   // global grain -> [begin, end) in grain_sites
     const int32_t *grain_sites; // local stored site indices, grain-major
     const int32_t *origin;
+    double *part;               // [G][n_parts][4]: sums of the parts of each grain's list
     double *grain_out;          // [G][4]
     double *sys_out;            // [S][4]
     double *moments;            // [S][5]
-    int n_grains, n_sys;
+    int n_grains, n_sys, n_parts;
 };
+// the parts' sums, then (launch_reduce_systems) the grains' and systems'
 int launch_reduce_grains(const RedArgs &a, void *stream);
 int launch_reduce_systems(const RedArgs &a, int accumulate_moments, int reset, void *stream);
 template <typename T>

@@ -155,14 +155,14 @@ int launch_cells_from_mesh(int prec, void *dst, const double *src, int src_nx, i
 }
 
 // ---------------------------------------------------------------- reductions
-// Sum of N values per thread over a workgroup of kSumBlock threads, into
-// thread 0: lanes of a wavefront by shuffles, then the wavefronts in order.
-constexpr int kSumBlock = 256;
+// Sum of N values per thread over a workgroup of B threads, into thread 0:
+// lanes of a wavefront by shuffles, then the wavefronts in order.
+constexpr int kSumBlock = 1024;
 
-template <int N>
+template <int B, int N>
 __device__ __forceinline__ void block_sum(double (&v)[N])
 {
-    __shared__ double part[N][kSumBlock / 64];
+    __shared__ double part[N][B / 64];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1)
 #pragma unroll
@@ -173,15 +173,9 @@ __device__ __forceinline__ void block_sum(double (&v)[N])
     if (threadIdx.x == 0)
         for (int k = 0; k < N; ++k) {
             v[k] = part[k][0];
-            for (int w = 1; w < kSumBlock / 64; ++w) v[k] += part[k][w];
+            for (int w = 1; w < B / 64; ++w) v[k] += part[k][w];
         }
 }
-
-// One block per grain walks the grain's site list (ascending site index),
-// keeps the sites inside the window, accumulates in FP64 per thread, and
-// reduces the block in a fixed tree order: deterministic, no atomics.
-constexpr int kRedBlock = 1024;
-constexpr int kRedUnroll = 4;  // sites per thread and pass (independent loads)
 
 __device__ __forceinline__ bool site_in_window(const SysDev &d, int org, int32_t local)
 {
@@ -191,20 +185,28 @@ __device__ __forceinline__ bool site_in_window(const SysDev &d, int org, int32_t
     return X >= org && X < org + d.nx;
 }
 
-// One workgroup per grain.  Each pass covers kRedUnroll * kRedBlock sites of
-// the grain's list: thread t takes sites t, t + kRedBlock, ... (coalesced),
+// Spin sums of the grains, each grain's site list (ascending site index) cut
+// into n_parts equal parts, one workgroup per part.  Each pass covers kRedUnroll
+// * kRedBlock sites: thread t takes sites t, t + kRedBlock, ... (coalesced),
 // loads them all, then adds them in that order; the workgroup then sums its
 // threads in a fixed tree.  The order depends only on the site list, so the
-// FP64 result is the same in every run.
+// FP64 result is the same in every run.  Bound by the latency of the gather
+// (index, then spins): one workgroup per grain left most of the chip idle (40
+// us for the 224 grains of a 400x200x33 window, 50 us for 32 isolated grains).
+constexpr int kRedBlock = 256;
+constexpr int kRedUnroll = 4;  // sites per thread and pass (independent loads)
+
 template <typename T>
-__global__ __launch_bounds__(kRedBlock) void k_reduce_grains(RedArgs a)
+__global__ __launch_bounds__(kRedBlock) void k_reduce_parts(RedArgs a)
 {
-    const int g = blockIdx.x;
+    const int g = blockIdx.x / a.n_parts, part = blockIdx.x - g * a.n_parts;
     const int s = a.grain_sys[g];
     const SysDev d = a.sys[s];
     const int org = d.track ? a.origin[s] : 0;
     const T *S = (const T *)a.S;
-    const int64_t k0 = a.grain_ptr[g], k1 = a.grain_ptr[g + 1];
+    const int64_t ka = a.grain_ptr[g], kb = a.grain_ptr[g + 1];
+    const int64_t len = (kb - ka + a.n_parts - 1) / a.n_parts;
+    const int64_t k0 = min(ka + part * len, kb), k1 = min(k0 + len, kb);
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     for (int64_t base = k0; base < k1; base += (int64_t)kRedUnroll * kRedBlock) {
         int32_t loc[kRedUnroll];
@@ -233,40 +235,55 @@ __global__ __launch_bounds__(kRedBlock) void k_reduce_grains(RedArgs a)
                 acc[3] += 1.0;
             }
     }
-    __shared__ double red[4][kRedBlock];
-    for (int k = 0; k < 4; ++k) red[k][threadIdx.x] = acc[k];
-    __syncthreads();
-    for (int off = kRedBlock / 2; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off)
-            for (int k = 0; k < 4; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + off];
-        __syncthreads();
-    }
+    block_sum<kRedBlock>(acc);
     if (threadIdx.x == 0)
-        for (int k = 0; k < 4; ++k) a.grain_out[4 * (int64_t)g + k] = red[k][0];
+        for (int k = 0; k < 4; ++k) a.part[4 * (int64_t)blockIdx.x + k] = acc[k];
 }
 
 int launch_reduce_grains(const RedArgs &a, void *stream)
 {
     if (a.n_grains == 0) return 0;
+    const dim3 grid((unsigned)a.n_grains * (unsigned)a.n_parts);
     if (a.prec == ASD_FP64)
-        hipLaunchKernelGGL(k_reduce_grains<double>, dim3(a.n_grains), dim3(kRedBlock), 0,
-                           (hipStream_t)stream, a);
+        hipLaunchKernelGGL(k_reduce_parts<double>, grid, dim3(kRedBlock), 0, (hipStream_t)stream, a);
     else
-        hipLaunchKernelGGL(k_reduce_grains<float>, dim3(a.n_grains), dim3(kRedBlock), 0,
-                           (hipStream_t)stream, a);
+        hipLaunchKernelGGL(k_reduce_parts<float>, grid, dim3(kRedBlock), 0, (hipStream_t)stream, a);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// per system: ordered sum over its grains; optional moment statistics of
-// m = |M| / N: samples, sum m, sum m^2, sum m^4
-__global__ void k_reduce_systems(RedArgs a, int moments, int reset)
+// One workgroup per system: every grain's sum from its parts in order (a
+// thread per grain up to kPartsThread parts, a wavefront per grain beyond),
+// then the system's from its grains in a fixed tree; optional moment
+// statistics of m = |M| / N: samples, sum m, sum m^2, sum m^4.  One thread
+// walking the 224 grains of a window took 28 us.
+constexpr int kPartsThread = 16;
+
+__global__ __launch_bounds__(kSumBlock) void k_reduce_systems(RedArgs a, int moments, int reset)
 {
-    int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= a.n_sys) return;
-    const SysDev d = a.sys[s];
+    const int s = blockIdx.x;
+    const int g0 = a.sys[s].grain_base, g1 = g0 + a.sys[s].n_grains, P = a.n_parts;
+    const bool by_wave = P > kPartsThread;
+    const int lane = threadIdx.x & 63;
     double t[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int g = d.grain_base; g < d.grain_base + d.n_grains; ++g)
-        for (int k = 0; k < 4; ++k) t[k] += a.grain_out[4 * (int64_t)g + k];
+    const int first = by_wave ? (int)(threadIdx.x >> 6) : (int)threadIdx.x;
+    for (int g = g0 + first; g < g1; g += by_wave ? kSumBlock / 64 : kSumBlock) {
+        const double *p = a.part + 4 * (int64_t)g * P;
+        double v[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int q = by_wave ? lane : 0; q < P; q += by_wave ? 64 : 1)
+            for (int k = 0; k < 4; ++k) v[k] += p[4 * q + k];
+        if (by_wave) {
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1)
+                for (int k = 0; k < 4; ++k) v[k] += __shfl_down(v[k], off);
+            if (lane > 0) continue;
+        }
+        for (int k = 0; k < 4; ++k) {
+            a.grain_out[4 * (int64_t)g + k] = v[k];
+            t[k] += v[k];
+        }
+    }
+    block_sum<kSumBlock>(t);
+    if (threadIdx.x != 0) return;
     for (int k = 0; k < 4; ++k) a.sys_out[4 * (int64_t)s + k] = t[k];
     if (moments) {
         double *mo = a.moments + 5 * (int64_t)s;
@@ -284,8 +301,8 @@ __global__ void k_reduce_systems(RedArgs a, int moments, int reset)
 int launch_reduce_systems(const RedArgs &a, int moments, int reset, void *stream)
 {
     if (a.n_sys == 0) return 0;
-    hipLaunchKernelGGL(k_reduce_systems, dim3((a.n_sys + 63) / 64), dim3(64), 0,
-                       (hipStream_t)stream, a, moments, reset);
+    hipLaunchKernelGGL(k_reduce_systems, dim3(a.n_sys), dim3(kSumBlock), 0, (hipStream_t)stream, a,
+                       moments, reset);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -302,7 +319,7 @@ __global__ __launch_bounds__(kSumBlock) void k_energy_finish(const double *parti
     double t[3] = {0.0, 0.0, 0.0};
     for (int b = b0 + (int)threadIdx.x; b < b1; b += kSumBlock)
         for (int k = 0; k < 3; ++k) t[k] += partial[3 * (int64_t)b + k];
-    block_sum(t);
+    block_sum<kSumBlock>(t);
     if (threadIdx.x == 0) {
         for (int k = 0; k < 3; ++k) out[4 * (int64_t)s + k] = t[k];
         out[4 * (int64_t)s + 3] = (t[0] + t[1]) + t[2];
