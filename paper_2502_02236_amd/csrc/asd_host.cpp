@@ -1007,6 +1007,17 @@ int asd_set_spins(asd_t *h, int32_t s, const void *src, int32_t on_device)
     return ASD_OK;
 }
 
+// p is ordinary device memory of the handle's device
+static bool on_own_device(const asd_t *h, const void *p)
+{
+    hipPointerAttribute_t at;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();  // an unknown pointer: left to the copy's own check
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == h->device;
+}
+
 int asd_get_spins(asd_t *h, int32_t s, void *dst, int32_t on_device)
 {
     if (!h || !dst) return fail(h, ASD_EINVAL, "NULL argument");
@@ -1015,6 +1026,14 @@ int asd_get_spins(asd_t *h, int32_t s, void *dst, int32_t on_device)
     const size_t nb = spin_bytes(h, s);
     const char *src = h->ws + h->L.off_S[h->cur];
     hipMemcpyKind kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
+    // memory of the handle's own device: the three rows in one launch; anything
+    // else a device copy takes (another device's memory) goes through the copies
+    if (on_device && on_own_device(h, dst)) {
+        const int rc = launch_copy_rows(dst, src + (size_t)d.base * h->elem, nb, (size_t)h->L.ncs * h->elem,
+                                        h->stream);
+        if (rc == 0) return ASD_OK;
+        if (rc != -2) return fail(h, ASD_EHIP, "spin copy launch failed: %s", hipGetErrorString(hipGetLastError()));
+    }
     for (int k = 0; k < 3; ++k)
         HIP_OK(h, hipMemcpyAsync((char *)dst + k * nb, src + ((size_t)k * h->L.ncs + d.base) * h->elem,
                                  nb, kind, h->stream));

@@ -189,6 +189,9 @@ int launch_cells_from_mesh(int prec, void *dst, const double *src, int src_nx, i
 // copy stored columns [x0, x0 + ncols) of system d from src to dst (both [3][ncs])
 int launch_copy_columns(int prec, void *dst, const void *src, int64_t ncs, const SysDev &d, int x0,
                         int ncols, void *stream);
+// three rows of row_bytes, stride_bytes apart at src, packed at dst (one
+// launch); -2 when dst is not aligned to four bytes
+int launch_copy_rows(void *dst, const void *src, size_t row_bytes, size_t stride_bytes, void *stream);
 // zero the spins of non-magnetic sites of system d in buf ([3][ncs])
 int launch_mask_spins(int prec, void *buf, int64_t ncs, const uint16_t *label, const SysDev &d,
                       void *stream);

@@ -57,3 +57,26 @@ def test_split_sums_match_host_sums(n, n_grains, prec):
     e = oracle_system(w, labels=lab).energy(S, 0)
     np.testing.assert_allclose(h.energy()[0], np.asarray(e), rtol=0, atol=4 * tol * 6 * w.J[0])
     h.close()
+
+
+# rows of 16-byte chunks, of 4-byte words, and a destination no chunk fits
+@pytest.mark.parametrize("nx", [3, 4, 13, 64])
+@pytest.mark.parametrize("shift", [0, 4, 8, 1], ids=lambda v: f"dst+{v}")
+@pytest.mark.parametrize("prec", [A.ASD_FP64, A.ASD_FP32], ids=["fp64", "fp32"])
+def test_device_copy_of_the_spins(gpu, nx, shift, prec):
+    torch = gpu
+    w = W.c1_plain_sc().scaled(nx=nx, ny=3, nz=5, bc=(0, 0, 0))
+    ins = [bridge.SystemInputs(w) for _ in range(2)]
+    h = A.Handle(bridge.params_for(w, prec), [i.desc for i in ins])
+    for k in range(2):
+        h.set_spins(W.random_spins(nx * 15, k), k)
+        ref = h.get_spins(k)
+        nb = ref.nbytes
+        buf = torch.zeros(nb + 64, dtype=torch.uint8, device="cuda")
+        torch.cuda.synchronize()
+        A.asd_get_spins(h.h, k, buf.data_ptr() + shift, True)
+        torch.cuda.synchronize()
+        got = buf.cpu().numpy()
+        assert got[shift:shift + nb].tobytes() == ref.tobytes()
+        assert not got[:shift].any() and not got[shift + nb:].any()
+    h.close()
