@@ -27,6 +27,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "asd.h"
@@ -55,6 +56,8 @@ struct MMArgs {
     int32_t step_off;
     void *m, *ua, *ub, *acc;  // [3][n] in the handle precision
     double *me, *alpha;       // per cell, filled by the parameter pass
+    void *coef;               // [4][n] (MMCoef, handle precision) for the one-launch step, or null
+    int32_t elem;             // bytes per value of the handle precision
     const double *ghost[2];   // x-face neighbours [ny*nz][3] (zero: none), or null
     // a held field (T) per cell, added at every stage: cell (i, j, k) reads
     // bd[d][(bd_off + i) + bd_nx (j + ny k)] of a mesh bd_nx cells long; or null
@@ -95,6 +98,31 @@ __device__ __forceinline__ double equilibrium_m(double T, double Tc, double b)
     return lo;
 }
 
+// temperature-dependent coefficients of cell c
+template <typename T>
+struct MMCoef {
+    T cex, can, alpha, gp;
+};
+
+template <typename T>
+__device__ __forceinline__ MMCoef<T> mm_coef(const MMArgs &a, int c)
+{
+    const double me = a.me[c], al = a.alpha[c];
+    return MMCoef<T>{(T)((2.0 * a.A0 * me) / a.Ms0), (T)((2.0 * a.K0 * (me * me)) / a.Ms0), (T)al,
+                     (T)(-a.gamma / (1.0 + al * al))};
+}
+
+template <typename T>
+__device__ __forceinline__ void mm_coef_out(const MMArgs &a, int c)
+{
+    const MMCoef<T> q = mm_coef<T>(a, c);
+    T *o = (T *)a.coef;
+    o[c] = q.cex;
+    o[(int64_t)a.n + c] = q.can;
+    o[2 * (int64_t)a.n + c] = q.alpha;
+    o[3 * (int64_t)a.n + c] = q.gp;
+}
+
 // m_e and alpha of every cell at time t = (step + frac) dt
 __global__ __launch_bounds__(kMMTile) void k_mm_params(MMArgs a, double frac)
 {
@@ -114,6 +142,11 @@ __global__ __launch_bounds__(kMMTile) void k_mm_params(MMArgs a, double frac)
     a.me[c] = equilibrium_m(T, a.Tc, a.b);
     const double Tr = T < a.Tc ? T : a.Tc;
     a.alpha[c] = a.lambda * (1.0 - Tr / (3.0 * a.Tc));
+    if (!a.coef) return;
+    if (a.elem == 8)
+        mm_coef_out<double>(a, c);
+    else
+        mm_coef_out<float>(a, c);
 }
 
 template <typename T>
@@ -132,6 +165,64 @@ __device__ __forceinline__ int64_t mm_nb(const MMArgs &a, int i, int j, int k, i
         c[ax] = (c[ax] + n[ax]) % n[ax];
     }
     return c[0] + (int64_t)n[0] * (c[1] + (int64_t)n[1] * c[2]);
+}
+
+// write-field polarity of the step
+template <typename T>
+__device__ __forceinline__ T mm_polarity(const MMArgs &a)
+{
+    const int64_t step = *a.step + a.step_off;
+    T pol = T(1);
+    if (a.n_bits > 0 && a.spb > 0) pol = a.bits[(step / a.spb) % a.n_bits] ? T(1) : T(-1);
+    return pol;
+}
+
+// lap + (u - mc) w
+template <typename T>
+__device__ __forceinline__ void mm_lap_add(T (&lap)[3], T ux, T uy, T uz, const M3<T> &mc, T w)
+{
+    lap[0] = lap[0] + (ux - mc.x) * w;
+    lap[1] = lap[1] + (uy - mc.y) * w;
+    lap[2] = lap[2] + (uz - mc.z) * w;
+}
+
+// direction across x face `face` (0: -x) of boundary cell (j, k), or null when
+// nothing lies there
+__device__ __forceinline__ const double *mm_ghost(const MMArgs &a, int face, int j, int k)
+{
+    const double *g = a.ghost[face];
+    if (!g) return nullptr;
+    g += 3 * ((int64_t)j + (int64_t)a.ny * k);
+    return g[0] == 0.0 && g[1] == 0.0 && g[2] == 0.0 ? nullptr : g;
+}
+
+// Landau-Lifshitz right-hand side gp (m x B + alpha m x (m x B)) of cell
+// (i, j, k) with the Laplacian lap
+template <typename T>
+__device__ __forceinline__ void mm_rhs(const MMArgs &a, const MMCoef<T> &q, T pol, const M3<T> &mc,
+                                       const T (&lap)[3], int i, int j, int k, T (&f)[3])
+{
+    T B[3];
+    B[0] = q.cex * lap[0] + pol * (T)a.B[0];
+    B[1] = q.cex * lap[1] + pol * (T)a.B[1];
+    B[2] = q.cex * lap[2] + pol * (T)a.B[2];
+    B[2] = B[2] + q.can * mc.z;
+    if (a.bd) {
+        const int64_t nb = (int64_t)a.bd_nx * a.ny * a.nz;
+        const int64_t o = (a.bd_off + i) + (int64_t)a.bd_nx * (j + (int64_t)a.ny * k);
+        B[0] = B[0] + (T)a.bd[o];
+        B[1] = B[1] + (T)a.bd[nb + o];
+        B[2] = B[2] + (T)a.bd[2 * nb + o];
+    }
+    const T cx = mc.y * B[2] - mc.z * B[1];
+    const T cy = mc.z * B[0] - mc.x * B[2];
+    const T cz = mc.x * B[1] - mc.y * B[0];
+    const T ddx = mc.y * cz - mc.z * cy;
+    const T ddy = mc.z * cx - mc.x * cz;
+    const T ddz = mc.x * cy - mc.y * cx;
+    f[0] = q.gp * (cx + q.alpha * ddx);
+    f[1] = q.gp * (cy + q.alpha * ddy);
+    f[2] = q.gp * (cz + q.alpha * ddz);
 }
 
 // stage s: k_s from the stage input (m for s = 0, else the buffer the
@@ -153,48 +244,15 @@ __device__ __forceinline__ void mm_stage_cell(const MMArgs &a, int s, int c)
             const T w = (T)a.ih2[ax];
             if (q < 0) {
                 // the region across an x face: its direction (zero: nothing there)
-                const double *g = ax == 0 ? a.ghost[d < 0 ? 0 : 1] : nullptr;
-                if (!g) continue;
-                const double *gv = g + 3 * ((int64_t)j + (int64_t)a.ny * k);
-                if (gv[0] == 0.0 && gv[1] == 0.0 && gv[2] == 0.0) continue;
-                lap[0] = lap[0] + ((T)gv[0] - mc.x) * w;
-                lap[1] = lap[1] + ((T)gv[1] - mc.y) * w;
-                lap[2] = lap[2] + ((T)gv[2] - mc.z) * w;
+                const double *gv = ax == 0 ? mm_ghost(a, d < 0 ? 0 : 1, j, k) : nullptr;
+                if (gv) mm_lap_add(lap, (T)gv[0], (T)gv[1], (T)gv[2], mc, w);
                 continue;
             }
-            lap[0] = lap[0] + (u[q] - mc.x) * w;
-            lap[1] = lap[1] + (u[n + q] - mc.y) * w;
-            lap[2] = lap[2] + (u[2 * n + q] - mc.z) * w;
+            mm_lap_add(lap, u[q], u[n + q], u[2 * n + q], mc, w);
         }
-    const int64_t step = *a.step + a.step_off;
-    T pol = T(1);
-    if (a.n_bits > 0 && a.spb > 0) pol = a.bits[(step / a.spb) % a.n_bits] ? T(1) : T(-1);
-    const double me = a.me[c];
-    const T cex = (T)((2.0 * a.A0 * me) / a.Ms0);
-    const T can = (T)((2.0 * a.K0 * (me * me)) / a.Ms0);
-    T B[3];
-    B[0] = cex * lap[0] + pol * (T)a.B[0];
-    B[1] = cex * lap[1] + pol * (T)a.B[1];
-    B[2] = cex * lap[2] + pol * (T)a.B[2];
-    B[2] = B[2] + can * mc.z;
-    if (a.bd) {
-        const int64_t nb = (int64_t)a.bd_nx * a.ny * a.nz;
-        const int64_t q = (a.bd_off + i) + (int64_t)a.bd_nx * (j + (int64_t)a.ny * k);
-        B[0] = B[0] + (T)a.bd[q];
-        B[1] = B[1] + (T)a.bd[nb + q];
-        B[2] = B[2] + (T)a.bd[2 * nb + q];
-    }
-    const double al = a.alpha[c];
-    const T alpha = (T)al;
-    const T gp = (T)(-a.gamma / (1.0 + al * al));
-    // Landau-Lifshitz right-hand side gp (m x B + alpha m x (m x B))
-    const T cx = mc.y * B[2] - mc.z * B[1];
-    const T cy = mc.z * B[0] - mc.x * B[2];
-    const T cz = mc.x * B[1] - mc.y * B[0];
-    const T ddx = mc.y * cz - mc.z * cy;
-    const T ddy = mc.z * cx - mc.x * cz;
-    const T ddz = mc.x * cy - mc.y * cx;
-    const T f[3] = {gp * (cx + alpha * ddx), gp * (cy + alpha * ddy), gp * (cz + alpha * ddz)};
+    const MMCoef<T> co = mm_coef<T>(a, c);
+    T f[3];
+    mm_rhs(a, co, mm_polarity<T>(a), mc, lap, i, j, k, f);
     const T dt = (T)a.dt;
     const T m0[3] = {m[c], m[n + c], m[2 * n + c]};
     if (s == 0) {
@@ -215,6 +273,199 @@ __device__ __forceinline__ void mm_stage_cell(const MMArgs &a, int s, int c)
         m[n + c] = v[1] / r;
         m[2 * n + c] = v[2] / r;
     }
+}
+
+// The whole RK4 step of a tile in one launch (a spot that does not move, so
+// that the coefficients hold through the step).  A workgroup owns TW x TW cell
+// columns of all nz cells; stage s is computed on the tile widened by 3 - s
+// columns, from a stage input held in LDS on the tile widened by 4 (two buffers,
+// swapped by the stages), so no stage needs another workgroup's.  A thread keeps
+// up to kMMCells cells of the tile widened by 3 with their m, sum of stages and
+// coefficients in registers.  The box of a buffer has a slot beyond every end of
+// the mesh that the tile reaches, so the stencil has no branch: it holds the
+// boundary cell's own value (an open face: a zero difference), the direction of
+// the region across an x face, or the periodic image.  Each cell's arithmetic
+// is that of mm_stage_cell in the same order (the open faces add zeros): the
+// results are equal bit for bit.  m is read from a.m and the new m written to
+// a.ua (neighbouring tiles still read a.m).
+//
+// Bound by latency: the four launches took 5-8 us each for 300x60x8 cells, with
+// gaps of 3-4 us between them (27 us per step); one launch takes 15.3 us.
+// Measured on the way: 32 us with run-time tile widths and a branch per
+// neighbour, 19.3 us with 512 threads of four cells each (a thread's cells run
+// one after the other, so more wavefronts of fewer cells hide more).
+constexpr int kMMThreads = 1024, kMMCells = 2, kMMHalo = 3;
+// tile widths: the widest whose widened columns fit kMMThreads * kMMCells cells
+// at 16, 14, 10, 8, 4 and 2 planes
+constexpr int kMMTiles[] = {5, 6, 8, 10, 16, 26};
+
+// mesh cell of column q along an axis (periodic image), or -1
+__device__ __forceinline__ int mm_image(int q, int len, int per)
+{
+    if (q >= 0 && q < len) return q;
+    if (!per) return -1;
+    q %= len;
+    return q < 0 ? q + len : q;
+}
+
+template <typename T, int TW>
+__device__ __forceinline__ void mm_step_tile(const MMArgs &a, int tile)
+{
+    extern __shared__ __align__(16) unsigned char mm_lds[];
+    constexpr int H = kMMHalo, W = TW + 2 * H, B = W + 2, SZ = B * B;  // widened tile, box, box plane
+    const int nz = a.nz, box = SZ * (nz + 2);
+    const int ntx = (a.nx + TW - 1) / TW;
+    const int ty = tile / ntx;
+    const int x0 = (tile - ty * ntx) * TW - H, y0 = ty * TW - H;  // the widened tile's first column
+    M3<T> *u = (M3<T> *)mm_lds, *v = u + box;
+    const int64_t n = a.n;
+    const T *m = (const T *)a.m;
+    for (int q = threadIdx.x; q < SZ * nz; q += kMMThreads) {
+        const int k = q / SZ, r = q - k * SZ, y = r / B, x = r - y * B;
+        const int i = mm_image(x0 - 1 + x, a.nx, a.per[0]), j = mm_image(y0 - 1 + y, a.ny, a.per[1]);
+        if (i < 0 || j < 0) continue;  // beyond an open end: its boundary cell's slot, below
+        const int64_t c = i + (int64_t)a.nx * (j + (int64_t)a.ny * k);
+        const M3<T> t{m[c], m[n + c], m[2 * n + c]};
+        u[q + SZ] = t;
+        // the slots beyond the ends along z
+        if (a.per[2]) {
+            if (k == 0) u[r + SZ * (nz + 1)] = t;
+            if (k == nz - 1) u[r] = t;
+        }
+    }
+    // the thread's cells of the widened tile; flags: the slots beyond the mesh
+    // that it fills with its own value (bits 0-5: -x +x -y +y -z +z) or, periodic
+    // along z, its image (bits 6, 7: first, last cell)
+    M3<T> m0[kMMCells], acc[kMMCells];
+    MMCoef<T> co[kMMCells];
+    int at[kMMCells], cell[kMMCells], in[kMMCells], flags[kMMCells];
+    const T *cf = (const T *)a.coef;
+#pragma unroll
+    for (int e = 0; e < kMMCells; ++e) {
+        const int q = threadIdx.x + e * kMMThreads;
+        const int k = q / (W * W), r = q - k * (W * W), y = r / W, x = r - y * W;
+        const int i = mm_image(x0 + x, a.nx, a.per[0]), j = mm_image(y0 + y, a.ny, a.per[1]);
+        at[e] = ((k + 1) * B + y + 1) * B + x + 1;
+        // how far inside the widened tile: the stages it takes part in
+        in[e] = k < nz && i >= 0 && j >= 0 ? min(min(x, W - 1 - x), min(y, W - 1 - y)) : -1;
+        cell[e] = 0;
+        flags[e] = 0;
+        acc[e] = M3<T>{T(0), T(0), T(0)};
+        m0[e] = acc[e];
+        co[e] = MMCoef<T>{T(0), T(0), T(0), T(0)};
+        if (in[e] < 0) continue;
+        // a periodic image is computed for its neighbours and written by its own tile
+        if (i != x0 + x || j != y0 + y) in[e] = min(in[e], H - 1);
+        const int c = cell[e] = i + a.nx * (j + a.ny * k);
+        m0[e] = M3<T>{m[c], m[n + c], m[2 * n + c]};
+        co[e] = MMCoef<T>{cf[c], cf[n + c], cf[2 * n + c], cf[3 * n + c]};
+        if (a.per[2]) {
+            flags[e] = (k == 0 ? 64 : 0) | (k == nz - 1 ? 128 : 0);
+        } else {
+            flags[e] = (k == 0 ? 16 : 0) | (k == nz - 1 ? 32 : 0);
+        }
+        if (!a.per[1]) flags[e] |= (j == 0 ? 4 : 0) | (j == a.ny - 1 ? 8 : 0);
+        if (!a.per[0])
+#pragma unroll
+            for (int face = 0; face < 2; ++face) {
+                if (i != (face == 0 ? 0 : a.nx - 1)) continue;
+                const int o = at[e] + (face == 0 ? -1 : 1);
+                if (const double *gv = mm_ghost(a, face, j, k)) {  // both buffers, for the whole step
+                    u[o] = v[o] = M3<T>{(T)gv[0], (T)gv[1], (T)gv[2]};
+                } else {
+                    flags[e] |= 1 << face;
+                }
+            }
+    }
+    // own value into the slots beyond the mesh
+    auto mirror = [&](M3<T> *d, int e, const M3<T> &t) {
+        const int o = at[e], fl = flags[e];
+        if (fl & 1) d[o - 1] = t;
+        if (fl & 2) d[o + 1] = t;
+        if (fl & 4) d[o - B] = t;
+        if (fl & 8) d[o + B] = t;
+        if (fl & 16) d[o - SZ] = t;
+        if (fl & 32) d[o + SZ] = t;
+        if (fl & 64) d[o + nz * SZ] = t;
+        if (fl & 128) d[o - nz * SZ] = t;
+    };
+#pragma unroll
+    for (int e = 0; e < kMMCells; ++e)
+        if (flags[e] & 63) mirror(u, e, m0[e]);
+    const T pol = mm_polarity<T>(a);
+    const T dt = (T)a.dt;
+    const T wx = (T)a.ih2[0], wy = (T)a.ih2[1], wz = (T)a.ih2[2];
+    __syncthreads();
+    for (int s = 0; s < 4; ++s) {
+#pragma unroll
+        for (int e = 0; e < kMMCells; ++e) {
+            if (in[e] < s) continue;  // stage s: the tile widened by H - s
+            const M3<T> *p = u + at[e];
+            const M3<T> mc = p[0];
+            T lap[3] = {T(0), T(0), T(0)};
+            mm_lap_add(lap, p[-1].x, p[-1].y, p[-1].z, mc, wx);
+            mm_lap_add(lap, p[1].x, p[1].y, p[1].z, mc, wx);
+            mm_lap_add(lap, p[-B].x, p[-B].y, p[-B].z, mc, wy);
+            mm_lap_add(lap, p[B].x, p[B].y, p[B].z, mc, wy);
+            mm_lap_add(lap, p[-SZ].x, p[-SZ].y, p[-SZ].z, mc, wz);
+            mm_lap_add(lap, p[SZ].x, p[SZ].y, p[SZ].z, mc, wz);
+            T f[3];
+            const int c = cell[e];
+            if (a.bd) {  // the held field's mesh is wider along x
+                const int jk = c / a.nx;
+                mm_rhs(a, co[e], pol, mc, lap, c - jk * a.nx, jk % a.ny, jk / a.ny, f);
+            } else {
+                mm_rhs(a, co[e], pol, mc, lap, 0, 0, 0, f);
+            }
+            if (s == 3) {
+                const T r[3] = {m0[e].x + (dt / T(6)) * (acc[e].x + f[0]),
+                                m0[e].y + (dt / T(6)) * (acc[e].y + f[1]),
+                                m0[e].z + (dt / T(6)) * (acc[e].z + f[2])};
+                const T l = sqrt((r[0] * r[0] + r[1] * r[1]) + r[2] * r[2]);
+                T *out = (T *)a.ua;
+                for (int d = 0; d < 3; ++d) out[d * n + c] = r[d] / l;
+                continue;
+            }
+            acc[e] = s == 0 ? M3<T>{f[0], f[1], f[2]}
+                            : M3<T>{acc[e].x + T(2) * f[0], acc[e].y + T(2) * f[1], acc[e].z + T(2) * f[2]};
+            const T h = s == 2 ? dt : T(0.5) * dt;
+            const M3<T> t{m0[e].x + h * f[0], m0[e].y + h * f[1], m0[e].z + h * f[2]};
+            v[at[e]] = t;
+            if (flags[e]) mirror(v, e, t);
+        }
+        __syncthreads();
+        M3<T> *t = u;
+        u = v;
+        v = t;
+    }
+}
+
+template <typename T, int TW>
+__global__ __launch_bounds__(kMMThreads) void k_mm_step(MMArgs a)
+{
+    mm_step_tile<T, TW>(a, blockIdx.x);
+}
+
+// two regions in one launch: blocks [0, blocks0) take region a0
+template <typename T, int TW>
+__global__ __launch_bounds__(kMMThreads) void k_mm_step_pair(MMArgs a0, MMArgs a1, int blocks0)
+{
+    if ((int)blockIdx.x < blocks0)
+        mm_step_tile<T, TW>(a0, blockIdx.x);
+    else
+        mm_step_tile<T, TW>(a1, blockIdx.x - blocks0);
+}
+
+// the new m of the one-launch step back to its place, for up to two regions (a
+// run of an odd number of steps)
+__global__ void k_mm_settle(uint32_t *d0, const uint32_t *s0, int64_t n0, uint32_t *d1,
+                            const uint32_t *s1, int64_t n1)
+{
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < n0)
+        d0[t] = s0[t];
+    else if (t - n0 < n1)
+        d1[t - n0] = s1[t - n0];
 }
 
 template <typename T>
@@ -433,8 +684,10 @@ struct asd_mm_t {
     int elem = 8;
     int64_t n = 0, step = 0;
     size_t off_m = 0, off_ua = 0, off_ub = 0, off_acc = 0, off_me = 0, off_al = 0,
-           off_step = 0, off_bits = 0, off_ghost[2] = {0, 0}, off_fsum = 0, off_fdir = 0, bytes = 0;
+           off_step = 0, off_bits = 0, off_ghost[2] = {0, 0}, off_fsum = 0, off_fdir = 0, off_coef = 0, bytes = 0;
     bool ghost_on[2] = {false, false};
+    bool alt = false;       // within a call: the current m is in the first stage buffer
+    int tile = 0;           // tile width of the one-launch step (0: the stage kernels only)
     const double *bd = nullptr;  // held field of the multiscale window's demagnetising field
     int32_t bd_nx = 0, bd_off = 0;
     bool params_valid = false;  // m_e, alpha current for a spot that does not move
@@ -481,6 +734,51 @@ static int mm_check(const asd_mm_params *p)
     return ASD_OK;
 }
 
+static size_t mm_tile_lds(int tile, int nz, int elem)
+{
+    const size_t B = tile + 2 * kMMHalo + 2;
+    return 2 * 3 * B * B * (nz + 2) * elem;
+}
+
+// Tile width of the one-launch step for regions of nx0 (and nx1) x ny columns
+// of nz cells, 0 for none: beyond 16 planes the tile that a workgroup holds gets
+// so small that recomputing its surroundings costs more than the launches.
+// Among the tiles whose widened columns fit the threads and whose boxes fit the
+// LDS, the one with the least (workgroups per CU, at least one) x (cells per
+// thread): small meshes take small tiles (every CU busy), large ones the largest
+// (least recomputation).
+static int mm_pick_tile(int nx0, int nx1, int ny, int nz, int elem)
+{
+    int pick = 0;
+    double best = 1e300;
+    for (int t : kMMTiles) {
+        const int nw = (t + 2 * kMMHalo) * (t + 2 * kMMHalo) * nz;
+        if (nw > kMMThreads * kMMCells || mm_tile_lds(t, nz, elem) > 128 * 1024) continue;
+        const double tiles = ((double)((nx0 + t - 1) / t) + (double)((nx1 + t - 1) / t)) *
+                             (double)((ny + t - 1) / t);
+        const double cost = std::max(1.0, tiles / 256.0) * ((nw + kMMThreads - 1) / kMMThreads);
+        if (cost < best) {
+            best = cost;
+            pick = t;
+        }
+    }
+    return pick;
+}
+
+// f with the compiled tile width
+template <class F>
+static void mm_with_tile(int tile, F f)
+{
+    switch (tile) {
+    case 5: f(std::integral_constant<int, 5>()); break;
+    case 6: f(std::integral_constant<int, 6>()); break;
+    case 8: f(std::integral_constant<int, 8>()); break;
+    case 10: f(std::integral_constant<int, 10>()); break;
+    case 16: f(std::integral_constant<int, 16>()); break;
+    default: f(std::integral_constant<int, 26>()); break;
+    }
+}
+
 static void mm_layout(const asd_mm_params *p, asd_mm_t *h)
 {
     const size_t n = (size_t)p->nx * p->ny * p->nz;
@@ -495,6 +793,8 @@ static void mm_layout(const asd_mm_params *p, asd_mm_t *h)
     h->off_ua = take(3 * n * e);
     h->off_ub = take(3 * n * e);
     h->off_acc = take(3 * n * e);
+    h->tile = mm_pick_tile(p->nx, 0, p->ny, p->nz, (int)e);
+    if (h->tile) h->off_coef = take(4 * n * e);
     h->off_me = take(n * sizeof(double));
     h->off_al = take(n * sizeof(double));
     h->off_step = take(sizeof(int64_t));
@@ -550,10 +850,12 @@ static MMArgs mm_args(const asd_mm_t *h, int step_off)
     a.bits = (const uint8_t *)(w + h->off_bits);
     a.step = (const int64_t *)(w + h->off_step);
     a.step_off = step_off;
-    a.m = w + h->off_m;
-    a.ua = w + h->off_ua;
+    a.m = w + (h->alt ? h->off_ua : h->off_m);
+    a.ua = w + (h->alt ? h->off_m : h->off_ua);
     a.ub = w + h->off_ub;
     a.acc = w + h->off_acc;
+    a.coef = h->tile ? w + h->off_coef : nullptr;
+    a.elem = h->elem;
     a.me = (double *)(w + h->off_me);
     a.alpha = (double *)(w + h->off_al);
     for (int f = 0; f < 2; ++f)
@@ -564,21 +866,65 @@ static MMArgs mm_args(const asd_mm_t *h, int step_off)
     return a;
 }
 
-// launches of one step (step_off after the device counter); the parameter
-// pass runs per stage for a moving spot, else once when the drive changed
+// the one-launch step serves a spot that does not move (m_e and alpha hold
+// through the step's stages)
+static bool mm_one_launch(const asd_mm_t *h)
+{
+    return h->tile > 0 && h->drive.spot_mode != ASD_SPOT_MOVING;
+}
+
+// m back to its place after one-launch steps: every call leaves it there, so
+// that captured work and copies find it at one address
+static int mm_settle(asd_mm_t *h, asd_mm_t *h2 = nullptr)
+{
+    asd_mm_t *r[2] = {h, h2};
+    uint32_t *d[2] = {nullptr, nullptr}, *u[2] = {nullptr, nullptr};
+    int64_t n[2] = {0, 0};
+    for (int k = 0; k < 2; ++k)
+        if (r[k] && r[k]->alt) {
+            d[k] = (uint32_t *)(r[k]->ws + r[k]->off_m);
+            u[k] = (uint32_t *)(r[k]->ws + r[k]->off_ua);
+            n[k] = 3 * r[k]->n * (r[k]->elem / 4);
+            r[k]->alt = false;
+        }
+    if (n[0] + n[1] == 0) return ASD_OK;
+    hipLaunchKernelGGL(k_mm_settle, dim3((unsigned)((n[0] + n[1] + 255) / 256)), dim3(256), 0, h->stream,
+                       d[0], u[0], n[0], d[1], u[1], n[1]);
+    MM_HIP(h, hipGetLastError());
+    return ASD_OK;
+}
+
+// launches of one step (step_off after the device counter): one for a spot
+// that does not move where the mesh allows it, else one per stage; the
+// parameter pass runs per stage for a moving spot, else once when the drive
+// changed
 static int mm_launch_step(asd_mm_t *h, int step_off, bool params_now)
 {
     const MMArgs a = mm_args(h, step_off);
     const dim3 grid((unsigned)((h->n + kMMTile - 1) / kMMTile)), blk(kMMTile);
     const bool moving = h->drive.spot_mode == ASD_SPOT_MOVING;
     const double frac[4] = {0.0, 0.5, 0.5, 1.0};
-    for (int s = 0; s < 4; ++s) {
-        if (moving ? (s != 2) : (s == 0 && params_now))
-            hipLaunchKernelGGL(k_mm_params, grid, blk, 0, h->stream, a, frac[s]);
-        if (h->elem == 8)
-            hipLaunchKernelGGL(k_mm_stage<double>, grid, blk, 0, h->stream, a, s);
-        else
-            hipLaunchKernelGGL(k_mm_stage<float>, grid, blk, 0, h->stream, a, s);
+    if (mm_one_launch(h)) {
+        if (params_now) hipLaunchKernelGGL(k_mm_params, grid, blk, 0, h->stream, a, 0.0);
+        const int t = h->tile;
+        const dim3 g((unsigned)(((a.nx + t - 1) / t) * ((a.ny + t - 1) / t)));
+        const size_t lds = mm_tile_lds(t, a.nz, h->elem);
+        mm_with_tile(t, [&](auto tw) {
+            if (h->elem == 8)
+                hipLaunchKernelGGL((k_mm_step<double, decltype(tw)::value>), g, dim3(kMMThreads), lds, h->stream, a);
+            else
+                hipLaunchKernelGGL((k_mm_step<float, decltype(tw)::value>), g, dim3(kMMThreads), lds, h->stream, a);
+        });
+        h->alt = !h->alt;
+    } else {
+        for (int s = 0; s < 4; ++s) {
+            if (moving ? (s != 2) : (s == 0 && params_now))
+                hipLaunchKernelGGL(k_mm_params, grid, blk, 0, h->stream, a, frac[s]);
+            if (h->elem == 8)
+                hipLaunchKernelGGL(k_mm_stage<double>, grid, blk, 0, h->stream, a, s);
+            else
+                hipLaunchKernelGGL(k_mm_stage<float>, grid, blk, 0, h->stream, a, s);
+        }
     }
     return hipGetLastError() == hipSuccess ? ASD_OK
                                             : mm_fail(h, ASD_EHIP, "micromagnetic launch failed: %s",
@@ -714,6 +1060,8 @@ int asd_mm_step(asd_mm_t *h, int64_t n)
             MM_HIP(h, hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
             int rc = ASD_OK;
             for (int t = 0; t < G && rc == ASD_OK; ++t) rc = mm_launch_step(h, t, false);
+            if (rc == ASD_OK) rc = mm_settle(h);
+            h->alt = false;  // nothing ran: m is where it was
             if (rc == ASD_OK) hipLaunchKernelGGL(k_mm_advance, dim3(1), dim3(1), 0, h->stream, step, (int64_t)G);
             hipError_t e = hipStreamEndCapture(h->stream, &g);
             if (rc) {
@@ -732,9 +1080,13 @@ int asd_mm_step(asd_mm_t *h, int64_t n)
     }
     for (int64_t t = 0; t < n - done; ++t) {
         int rc = mm_launch_step(h, (int)t, !h->params_valid);
-        if (rc) return rc;
+        if (rc) {
+            (void)mm_settle(h);
+            return rc;
+        }
         if (h->drive.spot_mode != ASD_SPOT_MOVING) h->params_valid = true;
     }
+    if (int rc = mm_settle(h)) return rc;
     if (n - done > 0)
         hipLaunchKernelGGL(k_mm_advance, dim3(1), dim3(1), 0, h->stream, step, n - done);
     MM_HIP(h, hipGetLastError());
@@ -787,9 +1139,10 @@ int asd_mm_get_face(asd_mm_t *h, int32_t face, double *dirs)
 }
 
 // one RK4 step of two regions on one stream (same precision, spots that do
-// not move): the launches of asd_mm_step(h, 1) for both, with the stages of
-// the two merged into one launch each
-static int mm_step_pair(asd_mm_t *L, asd_mm_t *R)
+// not move), step_off after their device counters: the launches of
+// asd_mm_step(h, 1) for both merged into one (one per stage where the
+// meshes do not take the one-launch step); leaves the regions unsettled
+static int mm_step_pair(asd_mm_t *L, asd_mm_t *R, int step_off)
 {
     asd_mm_t *r[2] = {L, R};
     for (asd_mm_t *h : r)
@@ -799,7 +1152,27 @@ static int mm_step_pair(asd_mm_t *L, asd_mm_t *R)
                                dim3(kMMTile), 0, h->stream, a, 0.0);
             h->params_valid = true;
         }
-    const MMArgs a0 = mm_args(L, 0), a1 = mm_args(R, 0);
+    const MMArgs a0 = mm_args(L, step_off), a1 = mm_args(R, step_off);
+    const int t = L->p.ny == R->p.ny && L->p.nz == R->p.nz && L->tile && R->tile
+                      ? mm_pick_tile(L->p.nx, R->p.nx, L->p.ny, L->p.nz, L->elem)
+                      : 0;
+    if (t) {
+        const int rows = (L->p.ny + t - 1) / t;
+        const int b0 = (L->p.nx + t - 1) / t * rows, b1 = (R->p.nx + t - 1) / t * rows;
+        const size_t lds = mm_tile_lds(t, L->p.nz, L->elem);
+        mm_with_tile(t, [&](auto tw) {
+            if (L->elem == 8)
+                hipLaunchKernelGGL((k_mm_step_pair<double, decltype(tw)::value>), dim3((unsigned)(b0 + b1)),
+                                   dim3(kMMThreads), lds, L->stream, a0, a1, b0);
+            else
+                hipLaunchKernelGGL((k_mm_step_pair<float, decltype(tw)::value>), dim3((unsigned)(b0 + b1)),
+                                   dim3(kMMThreads), lds, L->stream, a0, a1, b0);
+        });
+        MM_HIP(L, hipGetLastError());
+        L->alt = !L->alt;
+        R->alt = !R->alt;
+        return ASD_OK;
+    }
     const int b0 = (int)((L->n + kMMTile - 1) / kMMTile), b1 = (int)((R->n + kMMTile - 1) / kMMTile);
     const dim3 grid((unsigned)(b0 + b1)), blk(kMMTile);
     for (int s = 0; s < 4; ++s) {
@@ -808,11 +1181,7 @@ static int mm_step_pair(asd_mm_t *L, asd_mm_t *R)
         else
             hipLaunchKernelGGL(k_mm_stage_pair<float>, grid, blk, 0, L->stream, a0, a1, s, b0);
     }
-    hipLaunchKernelGGL(k_mm_advance_pair, dim3(1), dim3(1), 0, L->stream,
-                       (int64_t *)(L->ws + L->off_step), (int64_t *)(R->ws + R->off_step), (int64_t)1);
     MM_HIP(L, hipGetLastError());
-    L->step += 1;
-    R->step += 1;
     return ASD_OK;
 }
 
@@ -986,10 +1355,11 @@ static int multiscale_run(asd_t *atoms, int32_t sys, asd_mm_t *left, asd_mm_t *r
                 mm_drop_graph(m);  // graphs bake the face pointers in
             }
         }
-        const MMArgs aL = mm_args(left, 0), aR = mm_args(right, 0);
         const int bf = (nyz + 255) / 256;
-        for (int64_t t = 0; t < n; ++t) {
+        // one coupled step, t after the regions' device counters
+        auto coupled = [&](int64_t t) -> int {
             if (msd && (rc = msd_prepare(msd))) return rc;
+            const MMArgs aL = mm_args(left, 0), aR = mm_args(right, 0);
             if ((rc = coarse_grain_pair(atoms, sys, org, org + nx - cx, cx, cx, cy, cz, sumL, sumR)))
                 return rc;
             hipLaunchKernelGGL(k_mm_set_face_pair, dim3((unsigned)(2 * bf)), dim3(256), 0, left->stream,
@@ -1005,9 +1375,22 @@ static int multiscale_run(asd_t *atoms, int32_t sys, asd_mm_t *left, asd_mm_t *r
             if ((rc = set_columns_pair(atoms, sys, org - cx, org + nx, cx, cx, cy, cz, dirL, dirR)))
                 return rc;
             if ((rc = asd_step(atoms, 1))) return rc;
-            if ((rc = mm_step_pair(left, right))) return rc;
+            return mm_step_pair(left, right, (int)t);
+        };
+        int64_t done = 0;
+        rc = ASD_OK;
+        while (done < n && (rc = coupled(done)) == ASD_OK) ++done;
+        // the regions' m and counters, also after a failure part-way
+        const int rs = mm_settle(left, right);
+        if (done > 0) {
+            hipLaunchKernelGGL(k_mm_advance_pair, dim3(1), dim3(1), 0, left->stream,
+                               (int64_t *)(left->ws + left->off_step),
+                               (int64_t *)(right->ws + right->off_step), done);
+            MM_HIP(left, hipGetLastError());
+            left->step += done;
+            right->step += done;
         }
-        return ASD_OK;
+        return rc ? rc : rs;
     }
     for (int64_t t = 0; t < n; ++t) {
         if (msd && (rc = msd_prepare(msd))) return rc;
