@@ -1681,16 +1681,21 @@ void lattice_cell(const asd_t *h, double *dt, double edge[3])
     edge[2] = h->p.lattice == ASD_L10 ? h->p.c : h->p.a;
 }
 
-int coarse_grain_pair(asd_t *h, int32_t s, int32_t xa, int32_t xb, int32_t ncols, int32_t cx,
-                      int32_t cy, int32_t cz, double *outa, double *outb)
+int window_faces(asd_t *h, int32_t s, int32_t org, int32_t nx, int32_t cx, int32_t cy, int32_t cz,
+                 const RegionFace &left, const RegionFace &right)
 {
-    TransferArgs a, b;
-    int rc = transfer_args(h, s, xa, ncols, cx, cy, cz, &a);
-    if (rc || (rc = transfer_args(h, s, xb, ncols, cx, cy, cz, &b))) return rc;
-    if (!outa || !outb) return fail(h, ASD_EINVAL, "NULL output");
-    a.out = outa;
-    b.out = outb;
-    if (launch_coarse_grain_pair(a, b, h->stream)) return fail(h, ASD_EHIP, "coarse-grain launch failed");
+    WindowFaces f;
+    int rc;
+    const int32_t strip[2] = {org, org + nx - cx}, cols[2] = {org - cx, org + nx};
+    for (int k = 0; k < 2; ++k) {
+        if ((rc = transfer_args(h, s, strip[k], cx, cx, cy, cz, &f.strip[k]))) return rc;
+        if ((rc = transfer_args(h, s, cols[k], cx, cx, cy, cz, &f.cols[k]))) return rc;
+        f.cols[k].exact = 1;
+    }
+    f.region[0] = left;
+    f.region[1] = right;
+    if (launch_window_faces(f, h->stream)) return fail(h, ASD_EHIP, "window face launch failed");
+    h->stray_dirty = true;
     return ASD_OK;
 }
 
@@ -1736,21 +1741,6 @@ int32_t track_columns(const asd_t *h, int32_t s)
 {
     if (!h || s < 0 || s >= (int)h->sys.size() || !h->dev[s].track) return 0;
     return h->dev[s].sx;
-}
-
-int set_columns_pair(asd_t *h, int32_t s, int32_t xa, int32_t xb, int32_t ncols, int32_t cx,
-                     int32_t cy, int32_t cz, const double *ma, const double *mb)
-{
-    TransferArgs a, b;
-    int rc = transfer_args(h, s, xa, ncols, cx, cy, cz, &a);
-    if (rc || (rc = transfer_args(h, s, xb, ncols, cx, cy, cz, &b))) return rc;
-    if (!ma || !mb) return fail(h, ASD_EINVAL, "NULL cell direction");
-    a.mcell = ma;
-    b.mcell = mb;
-    a.exact = b.exact = 1;
-    if (launch_cone_columns_pair(a, b, h->stream)) return fail(h, ASD_EHIP, "column launch failed");
-    h->stray_dirty = true;
-    return ASD_OK;
 }
 
 }  // namespace asd

@@ -381,8 +381,11 @@ int launch_energy_finish(const double *partial, const SysDev *sys, int n_sys, do
 // count looks at the label and the loads of a row do not wait on it.
 constexpr int kCgX = 32, kCgZ = 8;
 
+// face (strips one coarse column wide): not the sums but their directions, as
+// the x-face neighbours of a region (zero where a cell has no magnetic site)
 template <typename T>
-__device__ __forceinline__ void coarse_grain_block(const TransferArgs &a, int bx, int by)
+__device__ __forceinline__ void coarse_grain_block(const TransferArgs &a, int bx, int by,
+                                                   double *face = nullptr)
 {
     const int tx = threadIdx.x % kCgX, tz = threadIdx.x / kCgX;
     const int ij = bx * kCgX + tx;  // cell i + ncx j of layer k
@@ -415,10 +418,16 @@ __device__ __forceinline__ void coarse_grain_block(const TransferArgs &a, int bx
     __syncthreads();
     if (tz == 0 && live) {
         const int64_t c = i + (int64_t)a.ncx * jk;
+        double t[4];
         for (int m = 0; m < 4; ++m) {
-            double t = red[m][0][tx];
-            for (int z = 1; z < kCgZ; ++z) t += red[m][z][tx];
-            a.out[4 * c + m] = t;
+            t[m] = red[m][0][tx];
+            for (int z = 1; z < kCgZ; ++z) t[m] += red[m][z][tx];
+        }
+        if (face) {
+            const double r = sqrt((t[0] * t[0] + t[1] * t[1]) + t[2] * t[2]);
+            for (int m = 0; m < 3; ++m) face[3 * c + m] = r > 0.0 ? t[m] / r : 0.0;
+        } else {
+            for (int m = 0; m < 4; ++m) a.out[4 * c + m] = t[m];
         }
     }
 }
@@ -427,33 +436,6 @@ template <typename T>
 __global__ __launch_bounds__(kCgX * kCgZ) void k_coarse_grain(TransferArgs a)
 {
     coarse_grain_block<T>(a, blockIdx.x, blockIdx.y);
-}
-
-// two strips of the same shape in one launch: blocks [0, gx) of a layer take
-// strip a0, the others strip a1
-template <typename T>
-__global__ __launch_bounds__(kCgX * kCgZ) void k_coarse_grain_pair(TransferArgs a0, TransferArgs a1,
-                                                                   int gx)
-{
-    if ((int)blockIdx.x < gx)
-        coarse_grain_block<T>(a0, blockIdx.x, blockIdx.y);
-    else
-        coarse_grain_block<T>(a1, blockIdx.x - gx, blockIdx.y);
-}
-
-int launch_coarse_grain_pair(const TransferArgs &a0, const TransferArgs &a1, void *stream)
-{
-    if (a0.ncx != a1.ncx || a0.ncy != a1.ncy || a0.ncell != a1.ncell || a0.prec != a1.prec) return -1;
-    if (a0.ncell == 0) return 0;
-    const int gx = (a0.ncx * a0.ncy + kCgX - 1) / kCgX;
-    const dim3 grid(2 * gx, a0.ncell / (a0.ncx * a0.ncy));
-    if (a0.prec == ASD_FP64)
-        hipLaunchKernelGGL(k_coarse_grain_pair<double>, grid, dim3(kCgX * kCgZ), 0,
-                           (hipStream_t)stream, a0, a1, gx);
-    else
-        hipLaunchKernelGGL(k_coarse_grain_pair<float>, grid, dim3(kCgX * kCgZ), 0,
-                           (hipStream_t)stream, a0, a1, gx);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 int launch_coarse_grain(const TransferArgs &a, void *stream)
@@ -489,7 +471,8 @@ __device__ __forceinline__ double cone_theta_max(double m)
 // 2017) around the cell direction.  FP64 throughout; both spin buffers
 // receive the result.
 template <typename T>
-__device__ __forceinline__ void cone_column_site(const TransferArgs &a, int64_t t)
+__device__ __forceinline__ void cone_column_site(const TransferArgs &a, int64_t t,
+                                                 const RegionFace *region = nullptr)
 {
     const int64_t n = (int64_t)a.per * a.ncols * a.d.ny * a.d.nz;
     if (t >= n) return;
@@ -502,8 +485,17 @@ __device__ __forceinline__ void cone_column_site(const TransferArgs &a, int64_t 
     const int64_t g = a.d.base + site;
     if (a.label[g] == kNoGrain) return;
     const int c = xx / a.cx + a.ncx * (y / a.cy + a.ncy * (z / a.cz));
-    const double mx = a.mcell[3 * (int64_t)c], my = a.mcell[3 * (int64_t)c + 1],
-                 mz = a.mcell[3 * (int64_t)c + 2];
+    double mx, my, mz;
+    if (region) {  // the region's cell beside coarse cell c
+        const int64_t q = region->col + (int64_t)region->nx * c;
+        mx = region->at(q, 0);
+        my = region->at(q, 1);
+        mz = region->at(q, 2);
+    } else {
+        mx = a.mcell[3 * (int64_t)c];
+        my = a.mcell[3 * (int64_t)c + 1];
+        mz = a.mcell[3 * (int64_t)c + 2];
+    }
     const double m = sqrt((mx * mx + my * my) + mz * mz);
     double nx = 0.0, ny = 0.0, nz = 1.0;
     if (m > 0.0) {
@@ -561,29 +553,49 @@ __global__ void k_cone_columns(TransferArgs a)
     cone_column_site<T>(a, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
-// two strips of the same shape in one launch: blocks [0, b0) take strip a0
+// Everything that crosses the two x faces of a multiscale window before a coupled
+// step, in one launch: the directions of the window's first and last coarse
+// column into the regions' face neighbours, and the regions' boundary cells into
+// the frozen columns just outside the window (exact directions).  All four read
+// the state at the start of the step and write what the others do not read.
+// Bound by the launches: as four kernels (sums, their directions, the regions'
+// faces, the columns) these took 19 us of a step with its gaps.
 template <typename T>
-__global__ void k_cone_columns_pair(TransferArgs a0, TransferArgs a1, int b0)
+__global__ __launch_bounds__(kCgX * kCgZ) void k_window_faces(WindowFaces f)
 {
-    if ((int)blockIdx.x < b0)
-        cone_column_site<T>(a0, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
-    else
-        cone_column_site<T>(a1, (int64_t)(blockIdx.x - b0) * blockDim.x + threadIdx.x);
+    int b = blockIdx.x;
+    const int cg = f.gx * f.layers;  // blocks per strip
+    if (b < 2 * cg) {
+        const int side = b < cg ? 0 : 1;
+        b -= side * cg;
+        const int k = b / f.gx;
+        coarse_grain_block<T>(f.strip[side], b - k * f.gx, k, f.region[side].ghost);
+        return;
+    }
+    b -= 2 * cg;
+    const int side = b < f.col_blocks ? 0 : 1;
+    b -= side * f.col_blocks;
+    cone_column_site<T>(f.cols[side], (int64_t)b * blockDim.x + threadIdx.x, &f.region[side]);
 }
 
-int launch_cone_columns_pair(const TransferArgs &a0, const TransferArgs &a1, void *stream)
+int launch_window_faces(WindowFaces &f, void *stream)
 {
-    const int64_t n = (int64_t)a0.per * a0.ncols * a0.d.ny * a0.d.nz;
-    if (n != (int64_t)a1.per * a1.ncols * a1.d.ny * a1.d.nz || a0.prec != a1.prec) return -1;
-    if (n == 0) return 0;
-    const int64_t b0 = (n + 255) / 256;
-    if (2 * b0 > INT32_MAX) return -1;
-    if (a0.prec == ASD_FP64)
-        hipLaunchKernelGGL(k_cone_columns_pair<double>, dim3((unsigned)(2 * b0)), dim3(256), 0,
-                           (hipStream_t)stream, a0, a1, (int)b0);
+    const TransferArgs &a = f.strip[0], &c = f.cols[0];
+    if (a.ncx != 1 || f.strip[1].ncx != 1 || a.ncell != f.strip[1].ncell || a.prec != f.strip[1].prec)
+        return -1;
+    const int64_t n = (int64_t)c.per * c.ncols * c.d.ny * c.d.nz;
+    const int threads = kCgX * kCgZ;
+    f.gx = (a.ncy + kCgX - 1) / kCgX;
+    f.layers = a.ncell / a.ncy;
+    const int64_t cb = (n + threads - 1) / threads, grid = 2 * ((int64_t)f.gx * f.layers + cb);
+    if (grid > INT32_MAX) return -1;
+    f.col_blocks = (int)cb;
+    if (a.prec == ASD_FP64)
+        hipLaunchKernelGGL(k_window_faces<double>, dim3((unsigned)grid), dim3(threads), 0,
+                           (hipStream_t)stream, f);
     else
-        hipLaunchKernelGGL(k_cone_columns_pair<float>, dim3((unsigned)(2 * b0)), dim3(256), 0,
-                           (hipStream_t)stream, a0, a1, (int)b0);
+        hipLaunchKernelGGL(k_window_faces<float>, dim3((unsigned)grid), dim3(threads), 0,
+                           (hipStream_t)stream, f);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -500,25 +500,6 @@ __global__ void k_mm_set_face(double *ghost, const double *vec, int stride, int 
     ghost[3 * c + 2] = r > 0.0 ? z / r : 0.0;
 }
 
-// both regions' faces in one launch: threads [0, nyz) take g0/v0, the next
-// nyz take g1/v1
-__global__ void k_mm_set_face_pair(double *g0, const double *v0, double *g1, const double *v1,
-                                   int stride, int nyz)
-{
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= 2 * nyz) return;
-    const bool second = t >= nyz;
-    const int c = second ? t - nyz : t;
-    const double *vec = second ? v1 : v0;
-    double *ghost = second ? g1 : g0;
-    const double x = vec[(int64_t)c * stride], y = vec[(int64_t)c * stride + 1],
-                 z = vec[(int64_t)c * stride + 2];
-    const double r = sqrt((x * x + y * y) + z * z);
-    ghost[3 * c] = r > 0.0 ? x / r : 0.0;
-    ghost[3 * c + 1] = r > 0.0 ? y / r : 0.0;
-    ghost[3 * c + 2] = r > 0.0 ? z / r : 0.0;
-}
-
 // directions of the cells of x face `face`
 template <typename T>
 __device__ __forceinline__ void mm_face_cell(const MMArgs &a, int face, double *dirs, int c)
@@ -533,17 +514,6 @@ template <typename T>
 __global__ void k_mm_get_face(MMArgs a, int face, double *dirs)
 {
     mm_face_cell<T>(a, face, dirs, blockIdx.x * blockDim.x + threadIdx.x);
-}
-
-// two regions' faces in one launch: blocks [0, b0) take region a0
-template <typename T>
-__global__ void k_mm_get_face_pair(MMArgs a0, int f0, double *d0, MMArgs a1, int f1, double *d1,
-                                   int b0)
-{
-    if ((int)blockIdx.x < b0)
-        mm_face_cell<T>(a0, f0, d0, blockIdx.x * blockDim.x + threadIdx.x);
-    else
-        mm_face_cell<T>(a1, f1, d1, (blockIdx.x - b0) * blockDim.x + threadIdx.x);
 }
 
 // What a region hands to the atomistic window by thermalisation (Sec. II):
@@ -1342,11 +1312,6 @@ static int multiscale_run(asd_t *atoms, int32_t sys, asd_mm_t *left, asd_mm_t *r
                       left->drive.spot_mode != ASD_SPOT_MOVING &&
                       right->drive.spot_mode != ASD_SPOT_MOVING;
     if (pair && n > 0) {
-        // the window's two boundary strips, the regions' facing faces and the
-        // frozen columns beside the window: one launch for both sides each
-        const int nyz = left->p.ny * left->p.nz;
-        double *sumL = (double *)(left->ws + left->off_fsum), *sumR = (double *)(right->ws + right->off_fsum);
-        double *dirL = (double *)(left->ws + left->off_fdir), *dirR = (double *)(right->ws + right->off_fdir);
         for (int f = 0; f < 2; ++f) {
             asd_mm_t *m = f == 0 ? left : right;
             const int face = f == 0 ? 1 : 0;
@@ -1355,24 +1320,15 @@ static int multiscale_run(asd_t *atoms, int32_t sys, asd_mm_t *left, asd_mm_t *r
                 mm_drop_graph(m);  // graphs bake the face pointers in
             }
         }
-        const int bf = (nyz + 255) / 256;
         // one coupled step, t after the regions' device counters
         auto coupled = [&](int64_t t) -> int {
             if (msd && (rc = msd_prepare(msd))) return rc;
-            const MMArgs aL = mm_args(left, 0), aR = mm_args(right, 0);
-            if ((rc = coarse_grain_pair(atoms, sys, org, org + nx - cx, cx, cx, cy, cz, sumL, sumR)))
-                return rc;
-            hipLaunchKernelGGL(k_mm_set_face_pair, dim3((unsigned)(2 * bf)), dim3(256), 0, left->stream,
-                               (double *)(left->ws + left->off_ghost[1]), sumL,
-                               (double *)(right->ws + right->off_ghost[0]), sumR, 4, nyz);
-            if (left->elem == 8)
-                hipLaunchKernelGGL(k_mm_get_face_pair<double>, dim3((unsigned)(2 * bf)), dim3(256), 0,
-                                   left->stream, aL, 1, dirL, aR, 0, dirR, bf);
-            else
-                hipLaunchKernelGGL(k_mm_get_face_pair<float>, dim3((unsigned)(2 * bf)), dim3(256), 0,
-                                   left->stream, aL, 1, dirL, aR, 0, dirR, bf);
-            MM_HIP(left, hipGetLastError());
-            if ((rc = set_columns_pair(atoms, sys, org - cx, org + nx, cx, cx, cy, cz, dirL, dirR)))
+            auto face = [](const asd_mm_t *m, int f) {
+                const MMArgs a = mm_args(m, 0);
+                return RegionFace{(double *)(m->ws + m->off_ghost[f]), a.m, m->n, m->elem, a.nx,
+                                  f == 0 ? 0 : a.nx - 1};
+            };
+            if ((rc = window_faces(atoms, sys, org, nx, cx, cy, cz, face(left, 1), face(right, 0))))
                 return rc;
             if ((rc = asd_step(atoms, 1))) return rc;
             return mm_step_pair(left, right, (int)t);
