@@ -103,6 +103,7 @@ struct asd_t {
     DemagDev dm{};            // demagnetising field (dm.on = 0: none)
     DemagDev dmT{};           // stray field of the frozen track (dmT.on = 0: none)
     bool stray_dirty = true;  // the frozen track changed since the stray field was computed
+    bool device_steps = false;    // steps were captured by the caller: the device counter rules
     bool external_field = false;  // the stray-field buffer holds a field set from outside
 };
 
@@ -1079,7 +1080,7 @@ static StepConsts make_consts(const asd_t *h)
 }
 
 template <typename T>
-static StepArgs<T> make_args(const asd_t *h, int cur, int step_off)
+static StepArgs<T> make_args(const asd_t *h, int cur, int step_off, int64_t abs_step = -1)
 {
     const Layout &L = h->L;
     char *w = h->ws;
@@ -1102,6 +1103,7 @@ static StepArgs<T> make_args(const asd_t *h, int cur, int step_off)
     a.bits = (const uint8_t *)(w + L.off_bits);
     a.zero_site = L.zero_site;
     a.step_off = step_off;
+    a.abs_step = abs_step;
     a.tile_cfg = h->tile_cfg;
     a.lattice = h->p.lattice;
     for (const HostSys &hs : h->sys)
@@ -1111,16 +1113,16 @@ static StepArgs<T> make_args(const asd_t *h, int cur, int step_off)
     return a;
 }
 
-static int launch_one(asd_t *h, int cur, int step_off)
+static int launch_one(asd_t *h, int cur, int step_off, int64_t abs_step = -1)
 {
     int rc;
     const bool fused = h->kernel == ASD_KERNEL_FUSED;
     const int blocks = fused ? h->n_ftiles : h->L.n_tiles;
     if (h->p.precision == ASD_FP64) {
-        StepArgs<double> a = make_args<double>(h, cur, step_off);
+        StepArgs<double> a = make_args<double>(h, cur, step_off, abs_step);
         rc = fused ? launch_fused_step_f64(a, blocks, h->stream) : launch_plain_step_f64(a, blocks, h->stream);
     } else {
-        StepArgs<float> a = make_args<float>(h, cur, step_off);
+        StepArgs<float> a = make_args<float>(h, cur, step_off, abs_step);
         rc = fused ? launch_fused_step_f32(a, blocks, h->stream) : launch_plain_step_f32(a, blocks, h->stream);
     }
     if (rc == -2) return fail(h, ASD_EUNSUPPORTED, "fused kernel not available for this lattice");
@@ -1176,6 +1178,21 @@ static int capture_graph(asd_t *h, int cur)
     return ASD_OK;
 }
 
+// Whether eager launches may carry their step: not while the caller captures
+// the stream into a graph of its own, whose replays must advance, and from
+// then on not at all (replays move the device counter past the host's).
+static bool host_steps(asd_t *h)
+{
+    if (h->device_steps) return false;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(h->stream, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (st != hipStreamCaptureStatusNone) h->device_steps = true;
+    return !h->device_steps;
+}
+
 int asd_step(asd_t *h, int64_t n)
 {
     if (!h) return fail(nullptr, ASD_EINVAL, "NULL handle");
@@ -1198,12 +1215,14 @@ int asd_step(asd_t *h, int64_t n)
         }
     }
     const int64_t rest = n - done;
+    const bool host = rest > 0 && host_steps(h);
     for (int64_t t = 0; t < rest; ++t) {
-        int rc = launch_one(h, h->cur, (int)t);
+        int rc = host ? launch_one(h, h->cur, (int)t, h->step) : launch_one(h, h->cur, (int)t);
         if (rc) return rc;
         h->cur = 1 - h->cur;
+        if (host) ++h->step;
     }
-    if (rest > 0) {
+    if (rest > 0 && !host) {
         if (launch_advance_step((int64_t *)(h->ws + h->L.off_step), rest, h->stream))
             return fail(h, ASD_EHIP, "advance launch failed");
         h->step += rest;
@@ -1627,11 +1646,13 @@ int asd_mc_sweep(asd_t *h, int64_t n)
     if (n == 0) return ASD_OK;
     // in place on the current buffer (a Heun step only reads the window of the
     // current buffer; the other one's window is overwritten)
+    const bool host = host_steps(h);
     for (int64_t t = 0; t < n; ++t) {
         int rc;
+        const int64_t abs = host ? h->step : -1;
         if (h->p.precision == ASD_FP64) {
             MCArgs<double> m;
-            m.st = make_args<double>(h, h->cur, (int)t);
+            m.st = make_args<double>(h, h->cur, (int)t, abs);
             m.st.tile_sys = (const int32_t *)(h->ws + h->L.off_tile);
             m.st.So = (double *)(h->ws + h->L.off_S[h->cur]);
             m.mu_s = h->p.mu_s;
@@ -1640,7 +1661,7 @@ int asd_mc_sweep(asd_t *h, int64_t n)
             rc = launch_mc_sweep_f64(m, h->L.n_tiles, h->stream);
         } else {
             MCArgs<float> m;
-            m.st = make_args<float>(h, h->cur, (int)t);
+            m.st = make_args<float>(h, h->cur, (int)t, abs);
             m.st.tile_sys = (const int32_t *)(h->ws + h->L.off_tile);
             m.st.So = (float *)(h->ws + h->L.off_S[h->cur]);
             m.mu_s = h->p.mu_s;
@@ -1649,7 +1670,9 @@ int asd_mc_sweep(asd_t *h, int64_t n)
             rc = launch_mc_sweep_f32(m, h->L.n_tiles, h->stream);
         }
         if (rc) return fail(h, ASD_EHIP, "Metropolis launch failed: %s", hipGetErrorString(hipGetLastError()));
+        if (host) ++h->step;
     }
+    if (host) return ASD_OK;
     if (launch_advance_step((int64_t *)(h->ws + h->L.off_step), n, h->stream))
         return fail(h, ASD_EHIP, "advance launch failed");
     h->step += n;

@@ -122,7 +122,9 @@ struct StepArgs {
     const int32_t *origin;    // window origin per system
     const uint8_t *bits;      // polarity bits
     int64_t zero_site;        // an always-zero slot
-    int32_t step_off;         // step = *step_base + step_off
+    int64_t abs_step;         // >= 0: the step itself, and *step_base is set to the one after it;
+                              // < 0 (captured launches): step = *step_base + step_off
+    int32_t step_off;
     int32_t tile_cfg;         // tile variant
     int32_t n_blocks;         // blocks of the launch (XCD-contiguous tile order)
     int32_t lattice;          // ASD_SC / ASD_L10
