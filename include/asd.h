@@ -76,7 +76,8 @@ extern "C" {
 #define ASD_SPOT_MOVING 1 /* spot centre x0 + v n dt (stored-lattice frame) */
 #define ASD_SPOT_LOCKED 2 /* spot centre origin*hx + x0: moves with the window */
 
-#define ASD_KERNEL_AUTO 0  /* fused kernel where available, else two-pass */
+#define ASD_KERNEL_AUTO 0  /* fused kernel where available (SC: the tile chosen by the
+                              lattices' sizes), else two-pass */
 #define ASD_KERNEL_PLAIN 1 /* two-pass: predictor kernel, corrector kernel */
 #define ASD_KERNEL_FUSED 2 /* one kernel per step, LDS tiles with recomputed halo
                               (open or periodic z; see asd_set_variant) */
@@ -364,13 +365,14 @@ int asd_philox(uint64_t seed, int32_t rounds, const uint32_t *ctr, uint32_t *out
  * shape, written otherwise (NULL: no cache). */
 int asd_autotune(asd_t *h, const char *cache_path);
 /* Force a variant: kernel ASD_KERNEL_PLAIN or ASD_KERNEL_FUSED, tile index
- * 0 .. asd_variant_count - 1 (0 = default), else ASD_EINVAL.  The fused
+ * 0 .. asd_variant_count - 1, else ASD_EINVAL.  The fused
  * kernels return ASD_EUNSUPPORTED (the handle keeps its variant) for a
  * system whose spins exceed 2 GiB per component, or when the anisotropy
  * varies per grain and some stored column crosses grains (labels varying
  * along z), or when the handle adds the demagnetising field (a whole-mesh
- * convolution between the two Heun stages); the two-pass kernels take every
- * system.  Two-pass tiles: 0 recomputes f(S) and the thermal field in the
+ * convolution between the two Heun stages) and the tile's z-chunks are thinner
+ * than six planes; the two-pass kernels take every system.  Two-pass tiles: 0
+ * recomputes f(S) and the thermal field in the
  * corrector, 1 stores them from the predictor, 2 (the default with the
  * demagnetising field; ASD_EUNSUPPORTED without it or for coarse cells wider
  * than 64 lattice cells) works on whole coarse cells and forms their spin

@@ -219,31 +219,27 @@ __device__ __forceinline__ void box_muller(uint32_t wr, uint32_t wt, double &gc,
 // ---------------------------------------------------------------- FP32
 namespace f32 {
 
-// Thermal-field Box-Muller pair in FP32 with sigma folded into the radius:
-// sigma r = sqrt(sigma^2 (-2 ln u_r)) = sqrt(ns2 log2 u_r) with
+// Thermal-field Box-Muller in FP32 with sigma folded into the radius, in polar
+// form: radii of the two pairs, sine and cosine of the first angle, cosine of the
+// second: sigma r = sqrt(sigma^2 (-2 ln u_r)) = sqrt(ns2 log2 u_r) with
 // ns2 = -2 ln2 sigma^2; u_r = w 2^-32 + 2^-33 rounded to FP32; v_log_f32 is
 // log2, v_sqrt_f32 the hardware square root (about 1 ulp), and v_sin_f32 /
 // v_cos_f32 take their argument in revolutions.
-__device__ __forceinline__ void box_muller_scaled(uint32_t wr, uint32_t wt, float ns2, float &gc,
-                                                  float &gs)
-{
-    const float TWO_M32 = 2.3283064365386962890625e-10f;
-    const float TWO_M33 = 1.16415321826934814453125e-10f;
-    float ur = __builtin_fmaf((float)wr, TWO_M32, TWO_M33);
-    float ut = (float)wt * TWO_M32;
-    float r = __builtin_amdgcn_sqrtf(ns2 * __builtin_amdgcn_logf(ur));
-    gc = r * __builtin_amdgcn_cosf(ut);
-    gs = r * __builtin_amdgcn_sinf(ut);
-}
+struct Polar2 {
+    float r1, c1, s1, r2, c2;
+};
 
-__device__ __forceinline__ float box_muller_scaled_cos(uint32_t wr, uint32_t wt, float ns2)
+__device__ __forceinline__ Polar2 box_muller_polar(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3,
+                                                   float ns2)
 {
     const float TWO_M32 = 2.3283064365386962890625e-10f;
     const float TWO_M33 = 1.16415321826934814453125e-10f;
-    float ur = __builtin_fmaf((float)wr, TWO_M32, TWO_M33);
-    float ut = (float)wt * TWO_M32;
-    float r = __builtin_amdgcn_sqrtf(ns2 * __builtin_amdgcn_logf(ur));
-    return r * __builtin_amdgcn_cosf(ut);
+    const float u1 = __builtin_fmaf((float)w0, TWO_M32, TWO_M33);
+    const float u2 = __builtin_fmaf((float)w2, TWO_M32, TWO_M33);
+    const float t1 = (float)w1 * TWO_M32, t2 = (float)w3 * TWO_M32;
+    return Polar2{__builtin_amdgcn_sqrtf(ns2 * __builtin_amdgcn_logf(u1)), __builtin_amdgcn_cosf(t1),
+                  __builtin_amdgcn_sinf(t1), __builtin_amdgcn_sqrtf(ns2 * __builtin_amdgcn_logf(u2)),
+                  __builtin_amdgcn_cosf(t2)};
 }
 
 // -2 ln 2 sigma^2 with sigma^2 = cth T

@@ -392,6 +392,37 @@ static void fused_tiles_of(const asd_params *p, const asd_system_desc *d, int ti
     if (tz) *tz = (d->nz + len - 1) / len;
 }
 
+// the fused variant a handle starts with: the least modelled time for the SC
+// step, the first of the table for L1_0 and with the demagnetising field
+static int fused_default(const asd_params *p, const std::vector<HostSys> &sys, bool demag)
+{
+    if (p->lattice != ASD_SC || demag) return 0;
+    const bool fp64 = p->precision == ASD_FP64;
+    int count, pick = 0;
+    const int *list = fused_default_list(fp64, &count);
+    double best = 1e300;
+    for (int q = 0; q < count; ++q) {
+        const FusedVariant f = fused_variant(fp64, list[q]);
+        double n = 0, all = 0, longest = 0;
+        for (const HostSys &hs : sys) {
+            int tx, ty, tz, len;
+            fused_tiles_of(p, &hs.desc, list[q], &tx, &ty, &tz, &len);
+            const bool per = hs.desc.bc_z == ASD_BC_PERIODIC;
+            // planes marched: a chunk's own and one beyond each end that is not a surface
+            const double xy = (double)tx * ty, planes = hs.desc.nz + 2.0 * (tz - (per ? 0 : 1));
+            n += xy * tz;
+            all += xy * planes;
+            longest = std::max(longest, len + std::min(2.0, per ? 2.0 : tz - 1.0));
+        }
+        const double t = fused_model_us(fp64, f, n, all, longest);
+        if (t < best) {
+            best = t;
+            pick = list[q];
+        }
+    }
+    return pick;
+}
+
 // partial-sum slots of the fused kernels with the demagnetising field, SC
 // variant v (stage: the halo-free stage kernels, else the one-launch step):
 // how many tiles one coarse cell can meet along x, y and z
@@ -561,6 +592,7 @@ static Layout make_layout(const asd_params *p, const asd_system_desc *sys, int n
         if (p->lattice == ASD_SC)
             for (int v = 0; v < fused_count(false, p->precision == ASD_FP64); ++v)
                 for (bool stage : {true, false}) {
+                    if (!fused_demag_chunk(fused_variant(p->precision == ASD_FP64, v))) continue;
                     int nsx, nsy, ns;
                     stage_slots(p, &sys[0], p->demag_cell, v, &nsx, &nsy, &ns, stage);
                     ns_max = std::max(ns_max, ns);
@@ -937,7 +969,7 @@ int asd_create(const asd_params *p, const asd_system_desc *sys, int32_t n_sys, v
     if (p->kernel != ASD_KERNEL_PLAIN) {
         const char *why = fused_unsupported(h);
         if (!why) {
-            int r3 = asd_set_variant(h, ASD_KERNEL_FUSED, 0);
+            int r3 = asd_set_variant(h, ASD_KERNEL_FUSED, fused_default(p, h->sys, L.dm.on != 0));
             if (r3) {
                 delete h;
                 return r3;
@@ -1914,6 +1946,12 @@ static int setup_fused_tiles(asd_t *h, int v)
     return upload_sysdev(h);
 }
 
+static bool fused_chunk_ok(const asd_t *h, int v)
+{
+    return !h->dm.on || h->p.lattice != ASD_SC ||
+           fused_demag_chunk(fused_variant(h->p.precision == ASD_FP64, v));
+}
+
 int asd_set_variant(asd_t *h, int32_t kernel, int32_t tile)
 {
     if (!h) return fail(nullptr, ASD_EINVAL, "NULL handle");
@@ -1929,6 +1967,8 @@ int asd_set_variant(asd_t *h, int32_t kernel, int32_t tile)
     }
     if (kernel == ASD_KERNEL_FUSED) {
         const char *why = fused_unsupported(h);
+        if (!why && !fused_chunk_ok(h, tile))
+            why = "the kernels with the demagnetising field take z-chunks of six planes or more";
         if (why) return fail(h, ASD_EUNSUPPORTED, "%s", why);
         int rc = setup_fused_tiles(h, tile);
         if (rc) return rc;
@@ -1981,6 +2021,8 @@ int asd_variant_name(asd_t *h, char *buf, size_t len)
         else if (h->dm.on)  // the predictor and corrector stages (open z only)
             snprintf(tmp, sizeof tmp, "k_fused_sc<%s, %d, %d, %d, false, 1>+k_fused_sc<%s, %d, %d, %d, false, 2>",
                      T, f.txe, f.waves, f.rows, T, f.txe, f.waves, f.rows);
+        else if (fused_ten_rounds(fp64, f.txe, h->p.philox_rounds, zper))
+            snprintf(tmp, sizeof tmp, "k_fused_sc<%s, %d, %d, %d, false, 4>", T, f.txe, f.waves, f.rows);
         else
             snprintf(tmp, sizeof tmp, "k_fused_sc<%s, %d, %d, %d, %s, 0>", T, f.txe, f.waves, f.rows,
                      zper ? "true" : "false");
@@ -2123,7 +2165,7 @@ int asd_autotune(asd_t *h, const char *cache_path)
         if (v != kCellRowVariant || !cell_rows_unsupported(h)) cands.push_back({ASD_KERNEL_PLAIN, v});
     if (!fused_unsupported(h))
         for (int v = 0; v < fused_count(h->p.lattice == ASD_L10, h->p.precision == ASD_FP64); ++v)
-            cands.push_back({ASD_KERNEL_FUSED, v});
+            if (fused_chunk_ok(h, v)) cands.push_back({ASD_KERNEL_FUSED, v});
     // pass 1: every candidate for 20 steps; pass 2: the three fastest, three
     // interleaved rounds of 60 steps each, ranked by their median
     double best = 1e30;

@@ -1,6 +1,8 @@
 // asd_variants.h -- kernel variants (host and device).
 #pragma once
 
+#include <stdint.h>
+
 namespace asd {
 
 // Two-pass kernel variants: 0 recomputes f(S) and the thermal field in the
@@ -18,24 +20,26 @@ struct FusedVariant {
     int txe, waves, rows, lz;
 };
 
-inline int fused_variant_count(bool fp64) { return fp64 ? 9 : 18; }
+inline int fused_variant_count(bool fp64) { return fp64 ? 13 : 26; }
 
-// Variant 0 is the default before any tuning (narrow tiles, z-chunks of 11:
-// enough workgroups for ~1M-site lattices); the others cover wider tiles for
-// large batches and the R = 2 and 16-lane shapes.  The twelve-wave tiles fill
-// a CU with one workgroup at three waves per SIMD (the occupancy of the R = 1
-// kernels' register count), on taller tiles: 32 x 24 extended columns
-// recompute 1.16x the interior where 64 x 8 recompute 1.38x.
+// Narrow tiles with short z-chunks serve lattices that leave the chip idle (every
+// plane of a march waits for the one before), wide ones without chunks large
+// batches (less recomputed halo, longer rows); fused_default picks by size.  The
+// twelve-wave tiles filled a CU with one workgroup at three waves per SIMD.
 inline FusedVariant fused_variant(bool fp64, int v)
 {
-    static const FusedVariant f32v[18] = {
+    static const FusedVariant f32v[26] = {
         {32, 4, 1, 11}, {64, 4, 2, 0},  {16, 4, 2, 11}, {32, 8, 1, 11}, {32, 4, 1, 17},
         {32, 8, 1, 17}, {32, 8, 1, 0},  {32, 4, 2, 11}, {64, 8, 2, 17}, {16, 4, 1, 11},
         {16, 8, 1, 11}, {16, 8, 1, 0},  {32, 8, 2, 8},  {32, 12, 1, 0}, {64, 12, 1, 0},
-        {16, 12, 1, 0}, {32, 12, 1, 11}, {32, 6, 1, 0}};
-    static const FusedVariant f64v[9] = {{32, 4, 1, 11}, {64, 4, 2, 0},  {32, 8, 1, 17},
+        {16, 12, 1, 0}, {32, 12, 1, 11}, {32, 6, 1, 0},  {64, 8, 1, 0},  {64, 16, 1, 0},
+        {64, 8, 1, 17}, {32, 4, 1, 6},  {32, 4, 1, 3},  {16, 4, 1, 3},  {32, 4, 1, 2},
+        {32, 4, 1, 1}};
+    static const FusedVariant f64v[13] = {{32, 4, 1, 11}, {64, 4, 2, 0},  {32, 8, 1, 17},
                                          {32, 4, 1, 0},  {32, 8, 1, 11}, {16, 4, 1, 11},
-                                         {32, 4, 2, 11}, {32, 12, 1, 0}, {32, 12, 1, 11}};
+                                         {32, 4, 2, 11}, {32, 12, 1, 0}, {32, 12, 1, 11},
+                                         {32, 4, 1, 6},  {32, 4, 1, 3},  {32, 4, 1, 2},
+                                         {32, 4, 1, 1}};
     const int n = fused_variant_count(fp64);
     if (v < 0 || v >= n) v = 0;
     return fp64 ? f64v[v] : f32v[v];
@@ -52,6 +56,51 @@ inline FusedVariant fused_l10_variant(bool fp64, int v)
     const int n = fused_l10_variant_count(fp64);
     if (v < 0 || v >= n) v = 0;
     return fp64 ? f64v[v] : f32v[v];
+}
+
+// the SC step that has the ten Philox rounds compiled in
+inline bool fused_ten_rounds(bool fp64, int txe, int rounds, bool zper)
+{
+    return !fp64 && txe == 64 && rounds == 10 && !zper;
+}
+
+// variants whose z-chunks the kernels with the demagnetising field take: thinner
+// ones would need a partial-sum slot per chunk that a coarse cell meets
+inline bool fused_demag_chunk(const FusedVariant &f) { return f.lz == 0 || f.lz >= 6; }
+
+// Modelled time (us) of a step of SC variant f: n tiles of planes_all xy planes in
+// all, the longest march planes long.  A tile's workgroups run in rounds of as many
+// as fit the CUs (waves per SIMD: 4 for 64 lanes in FP32, else 3, 2 in FP64); a
+// plane of a round takes a fixed latency plus its waves' share of a CU, at least
+// one wave's chain; a 64-lane tile's rows cost less per wave.  Fitted to 22 (FP32)
+// and 20 (FP64) lattices of 720 sites to 10.6M on MI355X: 8 % and 6 % rms; the
+// variant it picks is within 4 % of the fastest of the candidates on all but one
+// (7 %), where the former fixed choice (32 lanes, chunks of 11) was up to 2.0x
+// (2.8x) slower (FP32 and FP64: 16 x 16 x 8 sites 9.1 -> 5.6 us and 19.2 -> 9.2 us,
+// 64 x 64 x 20 11.3 -> 7.2 and 26.4 -> 14.0; FP32: four 400 x 200 x 33 windows 118
+// -> 96).
+inline double fused_model_us(bool fp64, const FusedVariant &f, double n, double planes_all, double planes)
+{
+    const double launch = fp64 ? 3.8 : 3.5, wave = fp64 ? 0.25 : (f.txe == 64 ? 0.71 : 1.0) * 0.086,
+                 chain = fp64 ? 0.85 : 0.35, latency = fp64 ? 1.0 : 0.345;
+    const int simd = fp64 ? 2 : (f.txe == 64 ? 4 : 3);
+    const int per_cu = 4 * simd / f.waves < 1 ? 1 : 4 * simd / f.waves;
+    const double waves = planes_all * f.waves / (n * planes);  // per tile, of its average march
+    auto round = [&](double per) {
+        const double t = wave * per * waves;
+        return planes * ((t > chain ? t : chain) + latency);
+    };
+    const int64_t slots = 256 * (int64_t)per_cu, full = (int64_t)n / slots, rest = (int64_t)n - full * slots;
+    return launch + full * round(per_cu) + (rest > 0 ? round((double)((rest + 255) / 256)) : 0.0);
+}
+
+// the variants fused_default chooses from (one column per lane)
+inline const int *fused_default_list(bool fp64, int *count)
+{
+    static const int f32[] = {25, 24, 22, 23, 21, 0, 4, 3, 5, 18, 19};
+    static const int f64[] = {12, 11, 10, 9, 0, 3, 4, 2};
+    *count = fp64 ? (int)(sizeof f64 / sizeof f64[0]) : (int)(sizeof f32 / sizeof f32[0]);
+    return fp64 ? f64 : f32;
 }
 
 inline int fused_count(bool l10, bool fp64)
