@@ -401,7 +401,7 @@ static int fused_default(const asd_params *p, const std::vector<HostSys> &sys, b
     int count, pick = 0;
     const int *list = fused_default_list(fp64, &count);
     double best = 1e300;
-    for (int q = 0; q < count; ++q) {
+    for (int q = 0; q < count; ++q) {  // the first of the list is the first of the table
         const FusedVariant f = fused_variant(fp64, list[q]);
         double n = 0, all = 0, longest = 0;
         for (const HostSys &hs : sys) {
@@ -416,7 +416,7 @@ static int fused_default(const asd_params *p, const std::vector<HostSys> &sys, b
         }
         const double t = fused_model_us(fp64, f, n, all, longest);
         if (t < best) {
-            best = t;
+            best = q ? t : t * fused_model_margin(fp64);
             pick = list[q];
         }
     }

@@ -74,8 +74,8 @@ inline bool fused_demag_chunk(const FusedVariant &f) { return f.lz == 0 || f.lz 
 // plane of a round takes a fixed latency plus its waves' share of a CU, at least
 // one wave's chain; a 64-lane tile's rows cost less per wave.  Fitted to 22 (FP32)
 // and 20 (FP64) lattices of 720 sites to 10.6M on MI355X: 8 % and 6 % rms; the
-// variant it picks is within 4 % of the fastest of the candidates on all but one
-// (7 %), where the former fixed choice (32 lanes, chunks of 11) was up to 2.0x
+// variant picked is within 4 % of the fastest of the candidates on all but three (7,
+// 8 and 17 %), where the former fixed choice (32 lanes, chunks of 11) was up to 2.0x
 // (2.8x) slower (FP32 and FP64: 16 x 16 x 8 sites 9.1 -> 5.6 us and 19.2 -> 9.2 us,
 // 64 x 64 x 20 11.3 -> 7.2 and 26.4 -> 14.0; FP32: four 400 x 200 x 33 windows 118
 // -> 96).
@@ -94,11 +94,17 @@ inline double fused_model_us(bool fp64, const FusedVariant &f, double n, double 
     return launch + full * round(per_cu) + (rest > 0 ? round((double)((rest + 255) / 256)) : 0.0);
 }
 
+// another variant than the first of the table is taken where the model puts it this
+// far below: with less a few lattices came out slower than with the first (FP64
+// 150 x 150 x 20 sites by 4 %, an FP32 step of 334 x 200 x 33 sites between two
+// regions' steps, whose launches leave the caches cold, by 13 %)
+inline double fused_model_margin(bool fp64) { return fp64 ? 0.9 : 0.85; }
+
 // the variants fused_default chooses from (one column per lane)
 inline const int *fused_default_list(bool fp64, int *count)
 {
-    static const int f32[] = {25, 24, 22, 23, 21, 0, 4, 3, 5, 18, 19};
-    static const int f64[] = {12, 11, 10, 9, 0, 3, 4, 2};
+    static const int f32[] = {0, 25, 24, 22, 23, 21, 4, 3, 5, 18, 19};
+    static const int f64[] = {0, 12, 11, 10, 9, 3, 4, 2};
     *count = fp64 ? (int)(sizeof f64 / sizeof f64[0]) : (int)(sizeof f32 / sizeof f32[0]);
     return fp64 ? f64 : f32;
 }
