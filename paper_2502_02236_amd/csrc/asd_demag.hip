@@ -146,6 +146,38 @@ __device__ __forceinline__ Cx<T> *lds_base()
     return (Cx<T> *)dm_lds;
 }
 
+// n values of src to dst in LDS, up to U loads of a thread in flight at a time
+template <int U, typename V>
+__device__ __forceinline__ void to_lds(V *dst, const V *__restrict__ src, int n)
+{
+    for (int q0 = threadIdx.x; q0 < n; q0 += U * blockDim.x) {
+        V v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int q = q0 + u * blockDim.x;
+            if (q < n) v[u] = src[q];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int q = q0 + u * blockDim.x;
+            if (q < n) dst[q] = v[u];
+        }
+    }
+}
+
+// the x twiddles of a row kernel, behind its two buffers in LDS: read from memory
+// in each of an FFT's stages they were much of its time (550 rows of 128 points:
+// k_dm_cells_x 8.5 -> 5.6 us with its partial sums' loads issued together, k_dm_x_out
+// 5.4 -> 4.9).  The caller synchronises.
+template <typename T>
+__device__ __forceinline__ Cx<T> *row_twiddles(const DemagDev &dm, Cx<T> *x)
+{
+    Cx<T> *tw = x + 6 * (1 << dm.lx);
+    to_lds<1>(tw, (const Cx<T> *)dm.tw[0], max((1 << dm.lx) >> 1, 1));
+    return tw;
+}
+inline size_t row_lds_bytes(int Px, size_t cb) { return (6 * (size_t)Px + std::max(Px >> 1, 1)) * cb; }
+
 // --- 1: cell sums of one (y, z) row of coarse cells, FFT along x.
 // Thread t takes cell i = t mod ncx and the lattice rows g, g + G, ... of that
 // cell (g = t / ncx, G = 256 / ncx row groups), so neighbouring lanes read
@@ -163,6 +195,7 @@ __global__ __launch_bounds__(kDmThreads) void k_dm_gather_x(DemagDev dm, const T
     const int org = d.track ? origin[s] : 0;
     const int per = d.kind == ASD_SC ? 1 : 2;
     Cx<T> *x = lds_base<T>(), *y = x + 3 * Px;
+    const Cx<T> *tw = row_twiddles<T>(dm, x);
     for (int q = threadIdx.x; q < 3 * Px; q += blockDim.x) x[q] = Cx<T>{T(0), T(0)};
     const int yb = j * dm.cy, zb = k * dm.cz;
     const int wy = min(dm.cy, d.ny - yb), wz = min(dm.cz, d.nz - zb);
@@ -206,7 +239,7 @@ __global__ __launch_bounds__(kDmThreads) void k_dm_gather_x(DemagDev dm, const T
         x[2 * Px + threadIdx.x].re = sz;
     }
     __syncthreads();
-    const Cx<T> *r = fft_lines<T, false>(x, y, 3, dm.lx, Px, (const Cx<T> *)dm.tw[0]);
+    const Cx<T> *r = fft_lines<T, false>(x, y, 3, dm.lx, Px, tw);
     Cx<T> *out = (Cx<T> *)dm.wx;
     const int Pxh = (Px >> 1) + 1;
     for (int q = threadIdx.x; q < 3 * Pxh; q += blockDim.x) {
@@ -225,19 +258,30 @@ __global__ __launch_bounds__(kDmThreads) void k_dm_cells_x(DemagDev dm, const U 
     const int j = blockIdx.x % dm.ncy, k = blockIdx.x / dm.ncy, s = blockIdx.y;
     Cx<T> *x = lds_base<T>(), *y = x + 3 * Px;
     const int ns = max(dm.ns, 1);  // partial sums per cell, added in slot order
-    for (int q = threadIdx.x; q < 3 * Px; q += blockDim.x) {
-        const int c = q >> dm.lx, i = q & (Px - 1);
-        const int64_t cell = i + (int64_t)dm.ncx * (j + (int64_t)dm.ncy * k);
+    // a thread per cell and component, eight partial sums' loads in flight
+    const int64_t cell0 = (int64_t)dm.ncx * (j + (int64_t)dm.ncy * k);
+    for (int q = threadIdx.x; q < 3 * dm.ncx; q += blockDim.x) {
+        const int c = q / dm.ncx, i = q - c * dm.ncx;
+        const U *p = src + ((int64_t)s * 3 + c) * ns * dm.ncell + cell0 + i;
         T v = T(0);
-        if (i < dm.ncx) {
-            const U *p = src + ((int64_t)s * 3 + c) * ns * dm.ncell + cell;
-            v = (T)p[0];
-            for (int sl = 1; sl < ns; ++sl) v = v + (T)p[(int64_t)sl * dm.ncell];
+        for (int s0 = 0; s0 < ns; s0 += 8) {
+            U t[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) t[u] = p[(int64_t)min(s0 + u, ns - 1) * dm.ncell];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (s0 + u < ns) v = s0 + u ? v + (T)t[u] : (T)t[u];
         }
-        x[q] = Cx<T>{v, T(0)};
+        x[c * Px + i] = Cx<T>{v, T(0)};
     }
+    const int pad = Px - dm.ncx;
+    for (int q = threadIdx.x; q < 3 * pad; q += blockDim.x) {
+        const int c = q / pad;
+        x[c * Px + dm.ncx + (q - c * pad)] = Cx<T>{T(0), T(0)};
+    }
+    const Cx<T> *tw = row_twiddles<T>(dm, x);
     __syncthreads();
-    const Cx<T> *r = fft_lines<T, false>(x, y, 3, dm.lx, Px, (const Cx<T> *)dm.tw[0]);
+    const Cx<T> *r = fft_lines<T, false>(x, y, 3, dm.lx, Px, tw);
     Cx<T> *out = (Cx<T> *)dm.wx;
     const int Pxh = (Px >> 1) + 1;
     for (int q = threadIdx.x; q < 3 * Pxh; q += blockDim.x) {
@@ -343,7 +387,13 @@ __global__ __launch_bounds__(kDmThreads) void k_dm_z(DemagDev dm)
 // column kx into LDS; FFT along y; per ky the field planes
 // as direct sums over the source planes with the tensor transformed along x
 // and y only, so the convolution along z needs neither padding nor
-// transforms; inverse FFT along y; the ncy rows back.  Lanes: four groups of
+// transforms; inverse FFT along y; the ncy rows back.  A mesh has a few dozen to a
+// hundred columns, so the chain of loads, stages and sums of a single workgroup is
+// what bounds it, not any rate.  SPLIT: three workgroups per column, one for each
+// component of the field; each repeats the forward transforms, does a third of the
+// sums and of the inverse ones, has its row of the tensor in LDS before the sums
+// ask for it, and writes to wy, since its neighbours still read wx.  All loads of
+// the column and the tensor are issued together.  Lanes: four groups of
 // Py, group q computing the planes q, q + 4, ... (wavefront-uniform, so the
 // unrolled sums need no divergent branches).
 constexpr int kDmYzThreads = 512;
@@ -387,12 +437,18 @@ __device__ __forceinline__ void yz_row(const T *__restrict__ ka, const T *__rest
     }
 }
 
-// the three output components of one ky (tensor at kt + (comp NCZ + d) oy;
-// xy and yz odd in ky, xz and yz imaginary and odd in dz)
-template <typename T, int NCZ, int Q0>
-__device__ __forceinline__ void yz_column(const T *__restrict__ kt, int oy, T sy,
-                                          const Cx<T> *__restrict__ r, Cx<T> *__restrict__ o,
-                                          int ls, int ky)
+// the three tensor components of row c of the tensor (xx yy zz xy xz yz)
+__device__ __forceinline__ int yz_comp(int c, int e)
+{
+    return c == e ? c : c + e + 2;
+}
+
+// output component C (all three: -1) of one ky, the planes Q0, Q0 + 4, ...; tensor
+// component comp at d oy of k(comp); xy and yz odd in ky, xz and yz imaginary and odd
+// in dz.  A single component goes to the first NCZ lines of o.
+template <typename T, int NCZ, int Q0, int C, class K>
+__device__ __forceinline__ void yz_column(const K &k, int oy, T sy, const Cx<T> *__restrict__ r,
+                                          Cx<T> *__restrict__ o, int ls, int ky)
 {
     // the sources of this ky (3 NCZ values) once
     Cx<T> m[3][NCZ];
@@ -400,83 +456,123 @@ __device__ __forceinline__ void yz_column(const T *__restrict__ kt, int oy, T sy
     for (int c = 0; c < 3; ++c)
 #pragma unroll
         for (int zs = 0; zs < NCZ; ++zs) m[c][zs] = r[(c * NCZ + zs) * ls + ky];
-    const int64_t cs = (int64_t)NCZ * oy;  // component stride
-    const T *kxx = kt, *kyy = kt + cs, *kzz = kt + 2 * cs, *kxy = kt + 3 * cs, *kxz = kt + 4 * cs,
-            *kyz = kt + 5 * cs;
-    yz_row<T, NCZ, Q0, false, false, true>(kxx, kxy, kxz, T(1), sy, T(1), oy, m, o, ls, ky, 0);
-    yz_row<T, NCZ, Q0, false, false, true>(kxy, kyy, kyz, sy, T(1), sy, oy, m, o, ls, ky, 1);
-    yz_row<T, NCZ, Q0, true, true, false>(kxz, kyz, kzz, T(1), sy, T(1), oy, m, o, ls, ky, 2);
+    if (C == 0 || C < 0)
+        yz_row<T, NCZ, Q0, false, false, true>(k(0), k(3), k(4), T(1), sy, T(1), oy, m, o, ls, ky, 0);
+    if (C == 1 || C < 0)
+        yz_row<T, NCZ, Q0, false, false, true>(k(3), k(1), k(5), sy, T(1), sy, oy, m, o, ls, ky, C < 0 ? 1 : 0);
+    if (C == 2 || C < 0)
+        yz_row<T, NCZ, Q0, true, true, false>(k(4), k(5), k(2), T(1), sy, T(1), oy, m, o, ls, ky, C < 0 ? 2 : 0);
 }
 
-template <typename T, int NCZ>
+template <typename T, int NCZ, int C, class K>
+__device__ __forceinline__ void yz_group(int q, const K &k, int oy, T sy, const Cx<T> *__restrict__ r,
+                                         Cx<T> *__restrict__ o, int ls, int ky)
+{
+    switch (q) {
+    case 0: yz_column<T, NCZ, 0, C>(k, oy, sy, r, o, ls, ky); break;
+    case 1: yz_column<T, NCZ, 1, C>(k, oy, sy, r, o, ls, ky); break;
+    case 2: yz_column<T, NCZ, 2, C>(k, oy, sy, r, o, ls, ky); break;
+    default: yz_column<T, NCZ, 3, C>(k, oy, sy, r, o, ls, ky); break;
+    }
+}
+
+template <typename T, int NCZ, bool SPLIT>
 __global__ __launch_bounds__(kDmYzThreads, sizeof(T) == 4 && NCZ <= 11 ? 4 : 2) void k_dm_yz(DemagDev dm)
 {
-    constexpr int Q = 4, nl = 3 * NCZ;
+    constexpr int Q = 4, nl = 3 * NCZ, U = 4, parts = SPLIT ? 3 : 1, no = nl / parts;
     const int Px = 1 << dm.lx, Py = 1 << dm.ly;
     const int Pxh = (Px >> 1) + 1;
     // blocks go round-robin over the eight XCDs: give each XCD a contiguous
     // range of columns, so that the neighbouring columns that share the
     // cache lines of wx are read through the same L2
-    const int nb = Pxh * dm.n_sys, per = gridDim.x >> 3;
+    const int nb = parts * Pxh * dm.n_sys, per = gridDim.x >> 3;
     const int tile = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
     if (tile >= nb) return;
-    const int kx = tile % Pxh, s = tile / Pxh;
-    const int ncy = dm.ncy, ls = Py + 1;
+    const int c = tile % parts, col = tile / parts;  // SPLIT: the output component
+    const int kx = col % Pxh, s = col / Pxh;
+    const int ncy = dm.ncy, ls = Py + 1, oy = (Py >> 1) + 1;
     Cx<T> *bx = lds_base<T>(), *by = bx + nl * ls, *twy = by + nl * ls;
+    const T *kt = (const T *)dm.K + (int64_t)kx * 6 * NCZ * oy;
     // line (c, z) row y of column kx at ((s 3 ncz + line) ncy + y) Pxh + kx
-    Cx<T> *w = (Cx<T> *)dm.wx + (int64_t)s * nl * ncy * Pxh + kx;
-    for (int q = threadIdx.x; q < nl * Py; q += blockDim.x) {
-        const int line = q >> dm.ly, yy = q & (Py - 1);
-        bx[line * ls + yy] = yy < ncy ? w[((int64_t)line * ncy + yy) * Pxh] : Cx<T>{T(0), T(0)};
+    const int64_t w0 = (int64_t)s * nl * ncy * Pxh + kx;
+    const Cx<T> *w = (const Cx<T> *)dm.wx + w0;
+    // the rows that are there, U loads of a thread in flight at a time; zeros beyond
+    for (int q0 = threadIdx.x; q0 < nl * ncy; q0 += U * blockDim.x) {
+        Cx<T> v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int q = q0 + u * blockDim.x;
+            if (q < nl * ncy) v[u] = w[(int64_t)q * Pxh];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int q = q0 + u * blockDim.x, line = q / ncy;
+            if (q < nl * ncy) bx[line * ls + (q - line * ncy)] = v[u];
+        }
+    }
+    const int pad = Py - ncy;
+    for (int q = threadIdx.x; q < nl * pad; q += blockDim.x) {
+        const int line = q / pad;
+        bx[line * ls + ncy + (q - line * pad)] = Cx<T>{T(0), T(0)};
     }
     // the twiddles of the y transforms in LDS
-    for (int q = threadIdx.x; q < max(Py >> 1, 1); q += blockDim.x) twy[q] = ((const Cx<T> *)dm.tw[1])[q];
+    to_lds<1>(twy, (const Cx<T> *)dm.tw[1], max(Py >> 1, 1));
+    // SPLIT: the three tensor components of this row too, by their column e
+    T *kl = (T *)(twy + max(Py >> 1, 1));
+    if constexpr (SPLIT)
+        for (int e = 0; e < 3; ++e) to_lds<4>(kl + e * NCZ * oy, kt + (int64_t)yz_comp(c, e) * NCZ * oy, NCZ * oy);
     __syncthreads();
     Cx<T> *r = fft_lines<T, false>(bx, by, nl, dm.ly, ls, twy);
     Cx<T> *o = r == bx ? by : bx;
-    const int oy = (Py >> 1) + 1;
-    const T *kt0 = (const T *)dm.K + (int64_t)kx * 6 * NCZ * oy;
     for (int t = threadIdx.x; t < Py * Q; t += blockDim.x) {
         const int q = t >> dm.ly, ky = t & (Py - 1);
         const int kyr = ky <= (Py >> 1) ? ky : Py - ky;
         const T sy = ky <= (Py >> 1) ? T(1) : T(-1);
-        const T *kt = kt0 + kyr;
-        switch (q) {
-        case 0: yz_column<T, NCZ, 0>(kt, oy, sy, r, o, ls, ky); break;
-        case 1: yz_column<T, NCZ, 1>(kt, oy, sy, r, o, ls, ky); break;
-        case 2: yz_column<T, NCZ, 2>(kt, oy, sy, r, o, ls, ky); break;
-        default: yz_column<T, NCZ, 3>(kt, oy, sy, r, o, ls, ky); break;
+        if constexpr (SPLIT) {
+            // component (c, e) of the tensor: e = the other index of the pair
+            auto k0 = [&](int p) { return kl + (p == 0 ? 0 : p - 2) * NCZ * oy + kyr; };
+            auto k1 = [&](int p) { return kl + (p == 3 ? 0 : p == 1 ? 1 : 2) * NCZ * oy + kyr; };
+            auto k2 = [&](int p) { return kl + (p == 4 ? 0 : p == 5 ? 1 : 2) * NCZ * oy + kyr; };
+            if (c == 0)
+                yz_group<T, NCZ, 0>(q, k0, oy, sy, r, o, ls, ky);
+            else if (c == 1)
+                yz_group<T, NCZ, 1>(q, k1, oy, sy, r, o, ls, ky);
+            else
+                yz_group<T, NCZ, 2>(q, k2, oy, sy, r, o, ls, ky);
+        } else {
+            auto k = [&](int p) { return kt + (int64_t)p * NCZ * oy + kyr; };
+            yz_group<T, NCZ, -1>(q, k, oy, sy, r, o, ls, ky);
         }
     }
     __syncthreads();
-    const Cx<T> *h = fft_lines<T, true>(o, r, nl, dm.ly, ls, twy);
-    for (int q = threadIdx.x; q < nl * ncy; q += blockDim.x) {
+    const Cx<T> *h = fft_lines<T, true>(o, r, no, dm.ly, ls, twy);
+    Cx<T> *out = (Cx<T> *)(SPLIT ? dm.wy : dm.wx) + w0 + (int64_t)c * no * ncy * Pxh;
+    for (int q = threadIdx.x; q < no * ncy; q += blockDim.x) {
         const int line = q / ncy, yy = q - line * ncy;
-        w[((int64_t)line * ncy + yy) * Pxh] = h[line * ls + yy];
+        out[(int64_t)q * Pxh] = h[line * ls + yy];
     }
 }
 
 // --- 5: inverse FFT along x of one (y, z) row, the field of its ncx cells
 template <typename T>
-__global__ __launch_bounds__(kDmThreads) void k_dm_x_out(DemagDev dm, int stage,
-                                                         const int32_t *origin)
+__global__ __launch_bounds__(kDmThreads) void k_dm_x_out(DemagDev dm, const void *rows,
+                                                         int stage, const int32_t *origin)
 {
     const int Px = 1 << dm.lx;
     const int j = blockIdx.x % dm.ncy, k = blockIdx.x / dm.ncy, s = blockIdx.y;
-    const Cx<T> *in = (const Cx<T> *)dm.wx;
+    const Cx<T> *in = (const Cx<T> *)rows;
     Cx<T> *x = lds_base<T>(), *y = x + 3 * Px;
     const int Pxh = (Px >> 1) + 1;
-    for (int q = threadIdx.x; q < 3 * Px; q += blockDim.x) {
-        const int c = q >> dm.lx, kx = q & (Px - 1);
-        if (kx < Pxh) {
-            x[q] = in[wx_at(dm, s, c, k, j, kx, Pxh)];
-        } else {  // X(Px - k) = conj X(k)
-            const Cx<T> v = in[wx_at(dm, s, c, k, j, Px - kx, Pxh)];
-            x[q] = Cx<T>{v.re, -v.im};
-        }
+    for (int q = threadIdx.x; q < 3 * Pxh; q += blockDim.x) {
+        const int c = q / Pxh, kx = q - c * Pxh;
+        const Cx<T> v = in[wx_at(dm, s, c, k, j, kx, Pxh)];
+        x[(c << dm.lx) + kx] = v;
+        // X(Px - k) = conj X(k)
+        if (kx && 2 * kx < Px) x[(c << dm.lx) + Px - kx] = Cx<T>{v.re, -v.im};
     }
+    const Cx<T> *tw = row_twiddles<T>(dm, x);
     __syncthreads();
-    const Cx<T> *r = fft_lines<T, true>(x, y, 3, dm.lx, Px, (const Cx<T> *)dm.tw[0]);
+    const Cx<T> *r = fft_lines<T, true>(x, y, 3, dm.lx, Px, tw);
     if (dm.stray) {
         // window cells i0 .. i0 + ncx_win - 1 of the track mesh
         const int org = origin[s];
@@ -509,16 +605,30 @@ int run_demag(const DemagDev &dm, const T *S, int64_t ncs, const SysDev *sys,
     const dim3 blk(kDmThreads);
     const dim3 grows(dm.ncy * dm.ncz, dm.n_sys);
     if (cells)
-        hipLaunchKernelGGL((k_dm_cells_x<T, U>), grows, blk, 2 * 3 * Px * cb, st, dm, cells);
+        hipLaunchKernelGGL((k_dm_cells_x<T, U>), grows, blk, row_lds_bytes(Px, cb), st, dm, cells);
     else
-        hipLaunchKernelGGL(k_dm_gather_x<T>, grows, blk, 2 * 3 * Px * cb, st, dm, S, ncs, sys,
+        hipLaunchKernelGGL(k_dm_gather_x<T>, grows, blk, row_lds_bytes(Px, cb), st, dm, S, ncs, sys,
                            origin);
     const int Pxh = (Px >> 1) + 1;
+    bool split = false;
     if (dm.yzf) {
-        const dim3 g((Pxh * dm.n_sys + 7) / 8 * 8), b(kDmYzThreads);
-        const size_t lds = demag_yz_lds_bytes(dm, (int)sizeof(T));
+        const size_t lds = demag_yz_lds_bytes(dm, (int)sizeof(T)),
+                     lds_split = lds + 3 * (size_t)dm.ncz * ((Py >> 1) + 1) * sizeof(T);
+        const int fit = (int)std::min<size_t>(160 * 1024 / lds_split, sizeof(T) == 4 && dm.ncz <= 11 ? 2 : 1);
+        // Three workgroups per column where all of them fit the chip at once (256 CUs;
+        // LDS and registers allow two workgroups per CU at most): 65 columns of 33
+        // lines of 128 rows 19.5 -> 15.4 us; 129 columns 20.7, as one workgroup of twice
+        // the threads each 19.9.  Past that the transforms done three times over would
+        // cost rounds.
+        split = 3 * Pxh * dm.n_sys <= 256 * fit;
+        const dim3 g((Pxh * dm.n_sys * (split ? 3 : 1) + 7) / 8 * 8), b(kDmYzThreads);
 #define ASD_YZ(N)                                                                                  \
-    case N: hipLaunchKernelGGL((k_dm_yz<T, N>), g, b, lds, st, dm); break;
+    case N:                                                                                        \
+        if (split)                                                                                 \
+            hipLaunchKernelGGL((k_dm_yz<T, N, true>), g, b, lds_split, st, dm);                    \
+        else                                                                                       \
+            hipLaunchKernelGGL((k_dm_yz<T, N, false>), g, b, lds, st, dm);                         \
+        break;
         switch (dm.ncz) {
             ASD_YZ(1) ASD_YZ(2) ASD_YZ(3) ASD_YZ(4) ASD_YZ(5) ASD_YZ(6) ASD_YZ(7) ASD_YZ(8)
             ASD_YZ(9) ASD_YZ(10) ASD_YZ(11) ASD_YZ(12) ASD_YZ(13) ASD_YZ(14) ASD_YZ(15) ASD_YZ(16)
@@ -532,7 +642,8 @@ int run_demag(const DemagDev &dm, const T *S, int64_t ncs, const SysDev *sys,
         hipLaunchKernelGGL(k_dm_z<T>, gz, blk, 2 * 3 * dm.xb_z * (Pz + 1) * cb, st, dm);
         hipLaunchKernelGGL((k_dm_y<T, true>), gy, blk, 2 * dm.xb_y * (Py + 1) * cb, st, dm);
     }
-    hipLaunchKernelGGL(k_dm_x_out<T>, grows, blk, 2 * 3 * Px * cb, st, dm, stage, origin);
+    hipLaunchKernelGGL(k_dm_x_out<T>, grows, blk, row_lds_bytes(Px, cb), st, dm, split ? dm.wy : dm.wx, stage,
+                       origin);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
