@@ -392,17 +392,18 @@ static void fused_tiles_of(const asd_params *p, const asd_system_desc *d, int ti
     if (tz) *tz = (d->nz + len - 1) / len;
 }
 
-// the fused variant a handle starts with: the least modelled time for the SC
-// step, the first of the table for L1_0 and with the demagnetising field
+// the fused variant a handle starts with: the least modelled time, the first of
+// the table with the demagnetising field
 static int fused_default(const asd_params *p, const std::vector<HostSys> &sys, bool demag)
 {
-    if (p->lattice != ASD_SC || demag) return 0;
-    const bool fp64 = p->precision == ASD_FP64;
+    if (demag) return 0;
+    const bool l10 = p->lattice != ASD_SC, fp64 = p->precision == ASD_FP64;
+    const FusedModel m = fused_model(l10, fp64);
     int count, pick = 0;
-    const int *list = fused_default_list(fp64, &count);
+    const int *list = fused_default_list(l10, fp64, &count);
     double best = 1e300;
     for (int q = 0; q < count; ++q) {  // the first of the list is the first of the table
-        const FusedVariant f = fused_variant(fp64, list[q]);
+        const FusedVariant f = fused_pick(l10, fp64, list[q]);
         double n = 0, all = 0, longest = 0;
         for (const HostSys &hs : sys) {
             int tx, ty, tz, len;
@@ -414,9 +415,9 @@ static int fused_default(const asd_params *p, const std::vector<HostSys> &sys, b
             all += xy * planes;
             longest = std::max(longest, len + std::min(2.0, per ? 2.0 : tz - 1.0));
         }
-        const double t = fused_model_us(fp64, f, n, all, longest);
+        const double t = fused_model_us(m, f, n, all, longest);
         if (t < best) {
-            best = q ? t : t * fused_model_margin(fp64);
+            best = q ? t : t * m.margin;
             pick = list[q];
         }
     }

@@ -1,4 +1,4 @@
-"""The SC step's tiles: whatever tile and z-chunk a step runs with, the same spins."""
+"""The step's tiles: whatever tile and z-chunk a step runs with, the same spins."""
 import numpy as np
 import pytest
 
@@ -17,9 +17,9 @@ def gpu():
     A.lib()
 
 
-def run(prec, dims, zper, rounds, variant):
+def run(prec, dims, zper, rounds, variant, base=W.c2_granular_slab):
     nx, ny, nz = dims
-    w = W.c2_granular_slab().scaled(nx=nx, ny=ny, nz=nz, x0=2e-9, y0=2e-9, grain_pitch=3e-9)
+    w = base().scaled(nx=nx, ny=ny, nz=nz, x0=2e-9, y0=2e-9, grain_pitch=3e-9)
     if zper:
         w = w.scaled(bc=w.bc[:2] + (W.BC_PERIODIC,))
     kernel = A.ASD_KERNEL_PLAIN if variant == "two-pass" else A.ASD_KERNEL_FUSED
@@ -63,3 +63,15 @@ def test_fp32_tiles_agree(dims, rounds, zper):
         np.testing.assert_array_equal(run(A.ASD_FP32, dims, zper, rounds, v), ref, err_msg=str(v))
     two = run(A.ASD_FP32, dims, zper, rounds, "two-pass")
     assert np.abs(ref - two).max() <= 3 * 8 * 2.0 ** -22
+
+
+# chunks of 1, 2, 3, 5 and 9 planes against one, two and more than nine; interiors of
+# 30 columns and 6 rows reached, passed and missed by one
+@pytest.mark.parametrize("dims,zper", [((30, 6, 2), False), ((31, 7, 4), False), ((31, 7, 4), True),
+                                       ((29, 5, 6), False), ((12, 13, 10), False), ((12, 13, 10), True)])
+def test_fp64_l10_tiles_equal_the_two_pass_step(dims, zper):
+    """FP64 rounds every operation of the definition: no tolerance."""
+    ref = run(A.ASD_FP64, dims, zper, 10, "two-pass", W.c3_l10_window)
+    for v in ["auto", 0, 1, 3, 4, 5, 6]:
+        np.testing.assert_array_equal(run(A.ASD_FP64, dims, zper, 10, v, W.c3_l10_window), ref,
+                                      err_msg=str(v))
