@@ -777,6 +777,13 @@ static void mm_layout(const asd_mm_params *p, asd_mm_t *h)
     h->bytes = off;
 }
 
+// the one-launch step serves a spot that does not move (m_e and alpha hold
+// through the step's stages)
+static bool mm_one_launch(const asd_mm_t *h)
+{
+    return h->tile > 0 && h->drive.spot_mode != ASD_SPOT_MOVING;
+}
+
 static MMArgs mm_args(const asd_mm_t *h, int step_off)
 {
     const asd_mm_params &p = h->p;
@@ -824,7 +831,9 @@ static MMArgs mm_args(const asd_mm_t *h, int step_off)
     a.ua = w + (h->alt ? h->off_m : h->off_ua);
     a.ub = w + h->off_ub;
     a.acc = w + h->off_acc;
-    a.coef = h->tile ? w + h->off_coef : nullptr;
+    // a moving spot's parameter passes, three a step, leave out what only the
+    // one-launch step reads (264 x 10 x 11 cells: 85.5 us a step with, 82.6 without)
+    a.coef = mm_one_launch(h) ? w + h->off_coef : nullptr;
     a.elem = h->elem;
     a.me = (double *)(w + h->off_me);
     a.alpha = (double *)(w + h->off_al);
@@ -834,13 +843,6 @@ static MMArgs mm_args(const asd_mm_t *h, int step_off)
     a.bd_nx = h->bd_nx;
     a.bd_off = h->bd_off;
     return a;
-}
-
-// the one-launch step serves a spot that does not move (m_e and alpha hold
-// through the step's stages)
-static bool mm_one_launch(const asd_mm_t *h)
-{
-    return h->tile > 0 && h->drive.spot_mode != ASD_SPOT_MOVING;
 }
 
 // m back to its place after one-launch steps: every call leaves it there, so
