@@ -76,7 +76,7 @@ extern "C" {
 #define ASD_SPOT_MOVING 1 /* spot centre x0 + v n dt (stored-lattice frame) */
 #define ASD_SPOT_LOCKED 2 /* spot centre origin*hx + x0: moves with the window */
 
-#define ASD_KERNEL_AUTO 0  /* fused kernel where available (SC: the tile chosen by the
+#define ASD_KERNEL_AUTO 0  /* fused kernel where available (the tile chosen by the
                               lattices' sizes), else two-pass */
 #define ASD_KERNEL_PLAIN 1 /* two-pass: predictor kernel, corrector kernel */
 #define ASD_KERNEL_FUSED 2 /* one kernel per step, LDS tiles with recomputed halo
