@@ -1041,15 +1041,22 @@ int asd_set_spins(asd_t *h, int32_t s, const void *src, int32_t on_device)
     return ASD_OK;
 }
 
-// p is ordinary device memory of the handle's device
-static bool on_own_device(const asd_t *h, const void *p)
+// [p, p + bytes) lies in one allocation of the handle's device, and that device is
+// the current one: a kernel may write there
+static bool on_own_device(const asd_t *h, void *p, size_t bytes)
 {
     hipPointerAttribute_t at;
-    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    int cur = -1;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess || at.type != hipMemoryTypeDevice ||
+        at.device != h->device || hipGetDevice(&cur) != hipSuccess || cur != h->device ||
+        hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess) {
         (void)hipGetLastError();  // an unknown pointer: left to the copy's own check
         return false;
     }
-    return at.type == hipMemoryTypeDevice && at.device == h->device;
+    const size_t at_byte = (size_t)((const char *)p - (const char *)base);
+    return at_byte <= size && bytes <= size - at_byte;
 }
 
 int asd_get_spins(asd_t *h, int32_t s, void *dst, int32_t on_device)
@@ -1061,8 +1068,9 @@ int asd_get_spins(asd_t *h, int32_t s, void *dst, int32_t on_device)
     const char *src = h->ws + h->L.off_S[h->cur];
     hipMemcpyKind kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
     // memory of the handle's own device: the three rows in one launch; anything
-    // else a device copy takes (another device's memory) goes through the copies
-    if (on_device && on_own_device(h, dst)) {
+    // else goes through the copies, which take another device's memory and refuse
+    // an allocation that ends before the rows do
+    if (on_device && on_own_device(h, dst, 3 * nb)) {
         const int rc = launch_copy_rows(dst, src + (size_t)d.base * h->elem, nb, (size_t)h->L.ncs * h->elem,
                                         h->stream);
         if (rc == 0) return ASD_OK;
