@@ -123,7 +123,11 @@ __device__ __forceinline__ void mm_coef_out(const MMArgs &a, int c)
     o[3 * (int64_t)a.n + c] = q.gp;
 }
 
-// m_e and alpha of every cell at time t = (step + frac) dt
+// m_e and alpha of every cell at time t = (step + frac) dt; COEF: the coefficients
+// of the one-launch step too.  A moving spot's passes, three a step, are compiled
+// without them: 264 x 10 x 11 cells in FP32 84.5 us a step with one kernel for both
+// and a branch, 82.4 so.
+template <bool COEF>
 __global__ __launch_bounds__(kMMTile) void k_mm_params(MMArgs a, double frac)
 {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
@@ -142,11 +146,12 @@ __global__ __launch_bounds__(kMMTile) void k_mm_params(MMArgs a, double frac)
     a.me[c] = equilibrium_m(T, a.Tc, a.b);
     const double Tr = T < a.Tc ? T : a.Tc;
     a.alpha[c] = a.lambda * (1.0 - Tr / (3.0 * a.Tc));
-    if (!a.coef) return;
-    if (a.elem == 8)
-        mm_coef_out<double>(a, c);
-    else
-        mm_coef_out<float>(a, c);
+    if constexpr (COEF) {
+        if (a.elem == 8)
+            mm_coef_out<double>(a, c);
+        else
+            mm_coef_out<float>(a, c);
+    }
 }
 
 template <typename T>
@@ -244,8 +249,11 @@ __device__ __forceinline__ void mm_stage_cell(const MMArgs &a, int s, int c)
             const T w = (T)a.ih2[ax];
             if (q < 0) {
                 // the region across an x face: its direction (zero: nothing there)
-                const double *gv = ax == 0 ? mm_ghost(a, d < 0 ? 0 : 1, j, k) : nullptr;
-                if (gv) mm_lap_add(lap, (T)gv[0], (T)gv[1], (T)gv[2], mc, w);
+                const double *g = ax == 0 ? a.ghost[d < 0 ? 0 : 1] : nullptr;
+                if (!g) continue;
+                const double *gv = g + 3 * ((int64_t)j + (int64_t)a.ny * k);
+                if (gv[0] == 0.0 && gv[1] == 0.0 && gv[2] == 0.0) continue;
+                mm_lap_add(lap, (T)gv[0], (T)gv[1], (T)gv[2], mc, w);
                 continue;
             }
             mm_lap_add(lap, u[q], u[n + q], u[2 * n + q], mc, w);
@@ -831,8 +839,6 @@ static MMArgs mm_args(const asd_mm_t *h, int step_off)
     a.ua = w + (h->alt ? h->off_m : h->off_ua);
     a.ub = w + h->off_ub;
     a.acc = w + h->off_acc;
-    // a moving spot's parameter passes, three a step, leave out what only the
-    // one-launch step reads (264 x 10 x 11 cells: 85.5 us a step with, 82.6 without)
     a.coef = mm_one_launch(h) ? w + h->off_coef : nullptr;
     a.elem = h->elem;
     a.me = (double *)(w + h->off_me);
@@ -843,6 +849,15 @@ static MMArgs mm_args(const asd_mm_t *h, int step_off)
     a.bd_nx = h->bd_nx;
     a.bd_off = h->bd_off;
     return a;
+}
+
+static void mm_launch_params(const asd_mm_t *h, const MMArgs &a, double frac)
+{
+    const dim3 grid((unsigned)((h->n + kMMTile - 1) / kMMTile)), blk(kMMTile);
+    if (a.coef)
+        hipLaunchKernelGGL(k_mm_params<true>, grid, blk, 0, h->stream, a, frac);
+    else
+        hipLaunchKernelGGL(k_mm_params<false>, grid, blk, 0, h->stream, a, frac);
 }
 
 // m back to its place after one-launch steps: every call leaves it there, so
@@ -877,7 +892,7 @@ static int mm_launch_step(asd_mm_t *h, int step_off, bool params_now)
     const bool moving = h->drive.spot_mode == ASD_SPOT_MOVING;
     const double frac[4] = {0.0, 0.5, 0.5, 1.0};
     if (mm_one_launch(h)) {
-        if (params_now) hipLaunchKernelGGL(k_mm_params, grid, blk, 0, h->stream, a, 0.0);
+        if (params_now) mm_launch_params(h, a, 0.0);
         const int t = h->tile;
         const dim3 g((unsigned)(((a.nx + t - 1) / t) * ((a.ny + t - 1) / t)));
         const size_t lds = mm_tile_lds(t, a.nz, h->elem);
@@ -891,7 +906,7 @@ static int mm_launch_step(asd_mm_t *h, int step_off, bool params_now)
     } else {
         for (int s = 0; s < 4; ++s) {
             if (moving ? (s != 2) : (s == 0 && params_now))
-                hipLaunchKernelGGL(k_mm_params, grid, blk, 0, h->stream, a, frac[s]);
+                mm_launch_params(h, a, frac[s]);
             if (h->elem == 8)
                 hipLaunchKernelGGL(k_mm_stage<double>, grid, blk, 0, h->stream, a, s);
             else
@@ -1022,9 +1037,7 @@ int asd_mm_step(asd_mm_t *h, int64_t n)
     const int G = h->p.graph_steps;
     if (G > 0 && n >= G) {
         if (!h->params_valid) {  // graphs never hold the parameter pass of a static spot
-            const MMArgs a = mm_args(h, 0);
-            hipLaunchKernelGGL(k_mm_params, dim3((unsigned)((h->n + kMMTile - 1) / kMMTile)),
-                               dim3(kMMTile), 0, h->stream, a, 0.0);
+            mm_launch_params(h, mm_args(h, 0), 0.0);
             h->params_valid = true;
         }
         if (!h->graph) {
@@ -1119,9 +1132,7 @@ static int mm_step_pair(asd_mm_t *L, asd_mm_t *R, int step_off)
     asd_mm_t *r[2] = {L, R};
     for (asd_mm_t *h : r)
         if (!h->params_valid) {
-            const MMArgs a = mm_args(h, 0);
-            hipLaunchKernelGGL(k_mm_params, dim3((unsigned)((h->n + kMMTile - 1) / kMMTile)),
-                               dim3(kMMTile), 0, h->stream, a, 0.0);
+            mm_launch_params(h, mm_args(h, 0), 0.0);
             h->params_valid = true;
         }
     const MMArgs a0 = mm_args(L, step_off), a1 = mm_args(R, step_off);
@@ -1408,9 +1419,7 @@ static int msd_prepare(asd_msd_t *m)
         // once by its parameter pass, is the one at every time
         const bool still = r->drive.spot_mode != ASD_SPOT_MOVING;
         if (still && !r->params_valid) {
-            const MMArgs a0 = mm_args(r, 0);
-            hipLaunchKernelGGL(k_mm_params, dim3((unsigned)((r->n + kMMTile - 1) / kMMTile)),
-                               dim3(kMMTile), 0, r->stream, a0, 0.0);
+            mm_launch_params(r, mm_args(r, 0), 0.0);
             r->params_valid = true;
         }
         rg[k]->a = mm_args(r, 0);
