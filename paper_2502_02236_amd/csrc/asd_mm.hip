@@ -32,6 +32,7 @@
 
 #include "asd.h"
 #include "asd_device.h"
+#include "asd_mm_tiles.h"
 #include "asd_pair.h"
 
 namespace asd {
@@ -302,10 +303,6 @@ __device__ __forceinline__ void mm_stage_cell(const MMArgs &a, int s, int c)
 // Measured on the way: 32 us with run-time tile widths and a branch per
 // neighbour, 19.3 us with 512 threads of four cells each (a thread's cells run
 // one after the other, so more wavefronts of fewer cells hide more).
-constexpr int kMMThreads = 1024, kMMCells = 2, kMMHalo = 3;
-// tile widths: the widest whose widened columns fit kMMThreads * kMMCells cells
-// at 16, 14, 10, 8, 4 and 2 planes
-constexpr int kMMTiles[] = {5, 6, 8, 10, 16, 26};
 
 // mesh cell of column q along an axis (periodic image), or -1
 __device__ __forceinline__ int mm_image(int q, int len, int per)
@@ -712,49 +709,27 @@ static int mm_check(const asd_mm_params *p)
     return ASD_OK;
 }
 
-static size_t mm_tile_lds(int tile, int nz, int elem)
-{
-    const size_t B = tile + 2 * kMMHalo + 2;
-    return 2 * 3 * B * B * (nz + 2) * elem;
-}
-
-// Tile width of the one-launch step for regions of nx0 (and nx1) x ny columns
-// of nz cells, 0 for none: beyond 16 planes the tile that a workgroup holds gets
-// so small that recomputing its surroundings costs more than the launches.
-// Among the tiles whose widened columns fit the threads and whose boxes fit the
-// LDS, the one with the least (workgroups per CU, at least one) x (cells per
-// thread): small meshes take small tiles (every CU busy), large ones the largest
-// (least recomputation).
-static int mm_pick_tile(int nx0, int nx1, int ny, int nz, int elem)
-{
-    int pick = 0;
-    double best = 1e300;
-    for (int t : kMMTiles) {
-        const int nw = (t + 2 * kMMHalo) * (t + 2 * kMMHalo) * nz;
-        if (nw > kMMThreads * kMMCells || mm_tile_lds(t, nz, elem) > 128 * 1024) continue;
-        const double tiles = ((double)((nx0 + t - 1) / t) + (double)((nx1 + t - 1) / t)) *
-                             (double)((ny + t - 1) / t);
-        const double cost = std::max(1.0, tiles / 256.0) * ((nw + kMMThreads - 1) / kMMThreads);
-        if (cost < best) {
-            best = cost;
-            pick = t;
-        }
-    }
-    return pick;
-}
-
-// f with the compiled tile width
+// f with the precision and the compiled tile width (FP64 has no width of 26)
 template <class F>
-static void mm_with_tile(int tile, F f)
+static void mm_with_tile(int elem, int tile, F f)
 {
-    switch (tile) {
-    case 5: f(std::integral_constant<int, 5>()); break;
-    case 6: f(std::integral_constant<int, 6>()); break;
-    case 8: f(std::integral_constant<int, 8>()); break;
-    case 10: f(std::integral_constant<int, 10>()); break;
-    case 16: f(std::integral_constant<int, 16>()); break;
-    default: f(std::integral_constant<int, 26>()); break;
-    }
+    auto width = [&](auto zero) {
+        using T = decltype(zero);
+        switch (tile) {
+        case 5: f(zero, std::integral_constant<int, 5>()); break;
+        case 6: f(zero, std::integral_constant<int, 6>()); break;
+        case 8: f(zero, std::integral_constant<int, 8>()); break;
+        case 10: f(zero, std::integral_constant<int, 10>()); break;
+        case 16: f(zero, std::integral_constant<int, 16>()); break;
+        default:
+            if constexpr (sizeof(T) == 4) f(zero, std::integral_constant<int, 26>());
+            break;
+        }
+    };
+    if (elem == 8)
+        width(0.0);
+    else
+        width(0.0f);
 }
 
 static void mm_layout(const asd_mm_params *p, asd_mm_t *h)
@@ -896,11 +871,9 @@ static int mm_launch_step(asd_mm_t *h, int step_off, bool params_now)
         const int t = h->tile;
         const dim3 g((unsigned)(((a.nx + t - 1) / t) * ((a.ny + t - 1) / t)));
         const size_t lds = mm_tile_lds(t, a.nz, h->elem);
-        mm_with_tile(t, [&](auto tw) {
-            if (h->elem == 8)
-                hipLaunchKernelGGL((k_mm_step<double, decltype(tw)::value>), g, dim3(kMMThreads), lds, h->stream, a);
-            else
-                hipLaunchKernelGGL((k_mm_step<float, decltype(tw)::value>), g, dim3(kMMThreads), lds, h->stream, a);
+        mm_with_tile(h->elem, t, [&](auto zero, auto tw) {
+            hipLaunchKernelGGL((k_mm_step<decltype(zero), decltype(tw)::value>), g, dim3(kMMThreads), lds,
+                               h->stream, a);
         });
         h->alt = !h->alt;
     } else {
@@ -1143,13 +1116,9 @@ static int mm_step_pair(asd_mm_t *L, asd_mm_t *R, int step_off)
         const int rows = (L->p.ny + t - 1) / t;
         const int b0 = (L->p.nx + t - 1) / t * rows, b1 = (R->p.nx + t - 1) / t * rows;
         const size_t lds = mm_tile_lds(t, L->p.nz, L->elem);
-        mm_with_tile(t, [&](auto tw) {
-            if (L->elem == 8)
-                hipLaunchKernelGGL((k_mm_step_pair<double, decltype(tw)::value>), dim3((unsigned)(b0 + b1)),
-                                   dim3(kMMThreads), lds, L->stream, a0, a1, b0);
-            else
-                hipLaunchKernelGGL((k_mm_step_pair<float, decltype(tw)::value>), dim3((unsigned)(b0 + b1)),
-                                   dim3(kMMThreads), lds, L->stream, a0, a1, b0);
+        mm_with_tile(L->elem, t, [&](auto zero, auto tw) {
+            hipLaunchKernelGGL((k_mm_step_pair<decltype(zero), decltype(tw)::value>), dim3((unsigned)(b0 + b1)),
+                               dim3(kMMThreads), lds, L->stream, a0, a1, b0);
         });
         MM_HIP(L, hipGetLastError());
         L->alt = !L->alt;
