@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <climits>
 #include <cmath>
 #include <cstdarg>
@@ -17,6 +18,7 @@
 #include "asd.h"
 #include "asd_internal.h"
 #include "asd_pair.h"
+#include "asd_tune.h"
 #include "asd_variants.h"
 
 using namespace asd;
@@ -2125,9 +2127,10 @@ static void tune_cache_store(const char *path, const std::string &key, int kerne
     rename(tmp.c_str(), path);
 }
 
-// time `steps` eager steps of the current variant (ms per step)
-static int time_variant(asd_t *h, int steps, double *ms)
+// time `steps` eager steps of the current variant from step step0 (ms per step)
+static int time_variant(asd_t *h, int64_t step0, int steps, double *ms)
 {
+    if (int rc = asd_set_step(h, step0)) return rc;
     hipEvent_t e0, e1;
     HIP_OK(h, hipEventCreate(&e0));
     HIP_OK(h, hipEventCreate(&e1));
@@ -2175,37 +2178,52 @@ int asd_autotune(asd_t *h, const char *cache_path)
     if (!fused_unsupported(h))
         for (int v = 0; v < fused_count(h->p.lattice == ASD_L10, h->p.precision == ASD_FP64); ++v)
             if (fused_chunk_ok(h, v)) cands.push_back({ASD_KERNEL_FUSED, v});
-    // pass 1: every candidate for 20 steps; pass 2: the three fastest, three
-    // interleaved rounds of 60 steps each, ranked by their median
-    double best = 1e30;
-    Cand pick = cands[0];
-    int rc = ASD_OK;
+    // the variant a handle starts with stays unless another is clearly ahead
+    const int kstart = fused_unsupported(h) ? ASD_KERNEL_PLAIN : ASD_KERNEL_FUSED;
+    const int tstart = kstart == ASD_KERNEL_FUSED ? fused_default(&h->p, h->sys, h->dm.on != 0)
+                                                  : (cell_rows_unsupported(h) ? 0 : kCellRowVariant);
+    size_t inc = 0;
+    while (inc + 1 < cands.size() && (cands[inc].kernel != kstart || cands[inc].tile != tstart)) ++inc;
+    // A card that was idle runs its first tenths of a second at lower clocks, where
+    // other tiles win (200 x 200 x 33 in FP32: chunks of 17 planes in seven of twelve
+    // runs, 19.5 us a step at full clocks against 18.4): step until that is over.
+    int rc = asd_set_variant(h, cands[inc].kernel, cands[inc].tile);
+    const auto t0 = std::chrono::steady_clock::now();
+    while (!rc && std::chrono::steady_clock::now() - t0 < std::chrono::milliseconds(300)) {
+        double ms = 0;
+        rc = time_variant(h, step0, 20, &ms);
+    }
+    // pass 1: every candidate for 20 steps; pass 2: the three fastest and the one that
+    // would stay, five interleaved rounds of 60 steps each
     std::vector<std::pair<double, size_t>> first;
     for (size_t i = 0; i < cands.size() && !rc; ++i) {
         double ms = 0;
         if ((rc = asd_set_variant(h, cands[i].kernel, cands[i].tile))) break;
-        if ((rc = time_variant(h, 20, &ms))) break;
+        if ((rc = time_variant(h, step0, 20, &ms))) break;
         first.push_back({ms, i});
     }
     std::sort(first.begin(), first.end());
-    const size_t nf = std::min<size_t>(3, first.size());
-    std::vector<std::vector<double>> rounds(nf);
-    for (int rd = 0; rd < 3 && !rc; ++rd)
-        for (size_t j = 0; j < nf && !rc; ++j) {
+    std::vector<size_t> final;
+    for (size_t j = 0; j < first.size() && j < 3; ++j) final.push_back(first[j].second);
+    size_t stay = 0;
+    while (stay < final.size() && final[stay] != inc) ++stay;
+    if (stay == final.size()) final.push_back(inc);
+    std::vector<std::vector<double>> rounds(final.size());
+    for (int rd = 0; rd < 5 && !rc; ++rd)
+        for (size_t j = 0; j < final.size() && !rc; ++j) {
             double ms = 0;
-            const Cand &c = cands[first[j].second];
+            const Cand &c = cands[final[j]];
             if ((rc = asd_set_variant(h, c.kernel, c.tile))) break;
-            if ((rc = time_variant(h, 60, &ms))) break;
+            if ((rc = time_variant(h, step0, 60, &ms))) break;
             rounds[j].push_back(ms);
         }
-    for (size_t j = 0; j < nf && !rc; ++j) {
-        std::vector<double> v = rounds[j];
-        std::sort(v.begin(), v.end());
-        const double med = v[v.size() / 2];
-        if (med < best) {
-            best = med;
-            pick = cands[first[j].second];
-        }
+    double best = 0.0;
+    Cand pick = cands[inc];
+    if (!rc) {
+        const size_t j = tune_pick(rounds, stay);
+        std::sort(rounds[j].begin(), rounds[j].end());
+        best = rounds[j][rounds[j].size() / 2];
+        pick = cands[final[j]];
     }
     h->graph_steps = gsteps;
     // restore the state into both ping-pong buffers and the step counter
