@@ -20,7 +20,7 @@ CASES = [
     ((30, 21, 14), (0, 1, 0), FP64, 5), ((30, 21, 15), (1, 0, 1), FP64, 0),
     ((161, 71, 7), (1, 0, 1), FP64, 6), ((301, 59, 8), (0, 0, 0), FP64, 8),
     ((211, 97, 3), (0, 1, 1), FP64, 10), ((301, 203, 1), (1, 1, 0), FP64, 16),
-    ((401, 203, 2), (0, 0, 1), FP64, 16), ((151, 61, 12), (0, 0, 0), FP64, 0),
+    ((401, 203, 2), (0, 0, 1), FP64, 16), ((201, 61, 12), (0, 0, 0), FP64, 0),
     ((97, 61, 8), (0, 1, 1), FP32, 5), ((31, 21, 16), (1, 0, 0), FP32, 5),
     ((31, 21, 17), (0, 0, 1), FP32, 0), ((161, 71, 7), (0, 1, 0), FP32, 6),
     ((131, 71, 10), (1, 0, 1), FP32, 8), ((211, 97, 4), (0, 0, 0), FP32, 10),
