@@ -769,7 +769,7 @@ def main():
                          "alu_ops_per_cell_step": 4 * MM_ALU_PER_STAGE,
                          "hbm": {"achieved": hbm, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                  "frac": hbm / HBM_PEAK_GBS, "bytes_per_cell": 6 * e},
-                         "traffic": None, "kernel": "k_mm_stage (four launches per step)"},
+                         "traffic": None, "kernel": "k_mm_step (one launch per step)"},
             "final_mz": r["mz"]}), flush=True)
         return
     if args.workload == "mc":
