@@ -264,7 +264,8 @@ __global__ __launch_bounds__(kDmThreads) void k_dm_cells_x(DemagDev dm, const U 
         const int c = q / dm.ncx, i = q - c * dm.ncx;
         const U *p = src + ((int64_t)s * 3 + c) * ns * dm.ncell + cell0 + i;
         T v = T(0);
-        for (int s0 = 0; s0 < ns; s0 += 8) {
+        if (ns == 1) v = (T)p[0];  // sums that come whole (eight loads of the one: 22.4 us, 21.1 so)
+        for (int s0 = 0; ns > 1 && s0 < ns; s0 += 8) {
             U t[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) t[u] = p[(int64_t)min(s0 + u, ns - 1) * dm.ncell];
@@ -393,7 +394,9 @@ __global__ __launch_bounds__(kDmThreads) void k_dm_z(DemagDev dm)
 // component of the field; each repeats the forward transforms, does a third of the
 // sums and of the inverse ones, has its row of the tensor in LDS before the sums
 // ask for it, and writes to wy, since its neighbours still read wx.  All loads of
-// the column and the tensor are issued together.  Lanes: four groups of
+// the column and the tensor are issued together; a whole column in one workgroup
+// keeps the plain loop (FP64, 11 planes of 512 x 128 points: 67.7 us before the
+// split, 72.3 with the batched loads, 70.5 so).  Lanes: four groups of
 // Py, group q computing the planes q, q + 4, ... (wavefront-uniform, so the
 // unrolled sums need no divergent branches).
 constexpr int kDmYzThreads = 512;
@@ -496,24 +499,31 @@ __global__ __launch_bounds__(kDmYzThreads, sizeof(T) == 4 && NCZ <= 11 ? 4 : 2) 
     // line (c, z) row y of column kx at ((s 3 ncz + line) ncy + y) Pxh + kx
     const int64_t w0 = (int64_t)s * nl * ncy * Pxh + kx;
     const Cx<T> *w = (const Cx<T> *)dm.wx + w0;
-    // the rows that are there, U loads of a thread in flight at a time; zeros beyond
-    for (int q0 = threadIdx.x; q0 < nl * ncy; q0 += U * blockDim.x) {
-        Cx<T> v[U];
+    if constexpr (SPLIT) {
+        // the rows that are there, U loads of a thread in flight at a time; zeros beyond
+        for (int q0 = threadIdx.x; q0 < nl * ncy; q0 += U * blockDim.x) {
+            Cx<T> v[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int q = q0 + u * blockDim.x;
-            if (q < nl * ncy) v[u] = w[(int64_t)q * Pxh];
-        }
+            for (int u = 0; u < U; ++u) {
+                const int q = q0 + u * blockDim.x;
+                if (q < nl * ncy) v[u] = w[(int64_t)q * Pxh];
+            }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int q = q0 + u * blockDim.x, line = q / ncy;
-            if (q < nl * ncy) bx[line * ls + (q - line * ncy)] = v[u];
+            for (int u = 0; u < U; ++u) {
+                const int q = q0 + u * blockDim.x, line = q / ncy;
+                if (q < nl * ncy) bx[line * ls + (q - line * ncy)] = v[u];
+            }
         }
-    }
-    const int pad = Py - ncy;
-    for (int q = threadIdx.x; q < nl * pad; q += blockDim.x) {
-        const int line = q / pad;
-        bx[line * ls + ncy + (q - line * pad)] = Cx<T>{T(0), T(0)};
+        const int pad = Py - ncy;
+        for (int q = threadIdx.x; q < nl * pad; q += blockDim.x) {
+            const int line = q / pad;
+            bx[line * ls + ncy + (q - line * pad)] = Cx<T>{T(0), T(0)};
+        }
+    } else {
+        for (int q = threadIdx.x; q < nl * Py; q += blockDim.x) {
+            const int line = q >> dm.ly, yy = q & (Py - 1);
+            bx[line * ls + yy] = yy < ncy ? w[((int64_t)line * ncy + yy) * Pxh] : Cx<T>{T(0), T(0)};
+        }
     }
     // the twiddles of the y transforms in LDS
     to_lds<1>(twy, (const Cx<T> *)dm.tw[1], max(Py >> 1, 1));
