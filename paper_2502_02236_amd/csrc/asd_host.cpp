@@ -1338,6 +1338,8 @@ static RedArgs red_args(const asd_t *h)
     a.moments = (double *)(w + L.off_mom);
     a.n_grains = L.n_grains;
     a.n_sys = (int)h->sys.size();
+    a.max_grains = 0;
+    for (const HostSys &hs : h->sys) a.max_grains = std::max(a.max_grains, (int)hs.n_grains);
     return a;
 }
 

@@ -211,6 +211,7 @@ struct RedArgs {
     double *sys_out;            // [S][4]
     double *moments;            // [S][5]
     int n_grains, n_sys, n_parts;
+    int max_grains;             // of a system
 };
 // the parts' sums, then (launch_reduce_systems) the grains' and systems'
 int launch_reduce_grains(const RedArgs &a, void *stream);

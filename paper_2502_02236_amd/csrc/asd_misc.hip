@@ -230,7 +230,10 @@ __device__ __forceinline__ bool site_in_window(const SysDev &d, int org, int32_t
 // (index, then spins): one workgroup per grain left most of the chip idle (40
 // us for the 224 grains of a 400x200x33 window, 50 us for 32 isolated grains).
 constexpr int kRedBlock = 256;
-constexpr int kRedUnroll = 4;  // sites per thread and pass (independent loads)
+// sites per thread and pass (independent loads): a part of up to 2048 sites in one
+// pass (64 systems of 2880 sites 18.2 us a moment sample, 19.6 in passes of four and
+// with k_reduce_systems in 1024 threads)
+constexpr int kRedUnroll = 8;
 
 template <typename T>
 __global__ __launch_bounds__(kRedBlock) void k_reduce_parts(RedArgs a)
@@ -287,14 +290,16 @@ int launch_reduce_grains(const RedArgs &a, void *stream)
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// One workgroup per system: every grain's sum from its parts in order (a
-// thread per grain up to kPartsThread parts, a wavefront per grain beyond),
+// One workgroup of B threads per system: every grain's sum from its parts in order
+// (a thread per grain up to kPartsThread parts, a wavefront per grain beyond),
 // then the system's from its grains in a fixed tree; optional moment
 // statistics of m = |M| / N: samples, sum m, sum m^2, sum m^4.  One thread
-// walking the 224 grains of a window took 28 us.
+// walking the 224 grains of a window took 28 us.  Systems whose grains one
+// wavefront covers get no more than that (the same sums: the others would add zeros).
 constexpr int kPartsThread = 16;
 
-__global__ __launch_bounds__(kSumBlock) void k_reduce_systems(RedArgs a, int moments, int reset)
+template <int B>
+__global__ __launch_bounds__(B) void k_reduce_systems(RedArgs a, int moments, int reset)
 {
     const int s = blockIdx.x;
     const int g0 = a.sys[s].grain_base, g1 = g0 + a.sys[s].n_grains, P = a.n_parts;
@@ -302,7 +307,7 @@ __global__ __launch_bounds__(kSumBlock) void k_reduce_systems(RedArgs a, int mom
     const int lane = threadIdx.x & 63;
     double t[4] = {0.0, 0.0, 0.0, 0.0};
     const int first = by_wave ? (int)(threadIdx.x >> 6) : (int)threadIdx.x;
-    for (int g = g0 + first; g < g1; g += by_wave ? kSumBlock / 64 : kSumBlock) {
+    for (int g = g0 + first; g < g1; g += by_wave ? B / 64 : B) {
         const double *p = a.part + 4 * (int64_t)g * P;
         double v[4] = {0.0, 0.0, 0.0, 0.0};
         for (int q = by_wave ? lane : 0; q < P; q += by_wave ? 64 : 1)
@@ -318,7 +323,7 @@ __global__ __launch_bounds__(kSumBlock) void k_reduce_systems(RedArgs a, int mom
             t[k] += v[k];
         }
     }
-    block_sum<kSumBlock>(t);
+    block_sum<B>(t);
     if (threadIdx.x != 0) return;
     for (int k = 0; k < 4; ++k) a.sys_out[4 * (int64_t)s + k] = t[k];
     if (moments) {
@@ -337,8 +342,13 @@ __global__ __launch_bounds__(kSumBlock) void k_reduce_systems(RedArgs a, int mom
 int launch_reduce_systems(const RedArgs &a, int moments, int reset, void *stream)
 {
     if (a.n_sys == 0) return 0;
-    hipLaunchKernelGGL(k_reduce_systems, dim3(a.n_sys), dim3(kSumBlock), 0, (hipStream_t)stream, a,
-                       moments, reset);
+    const int threads = a.n_parts > kPartsThread ? 64 * a.max_grains : a.max_grains;
+    if (threads <= 64)
+        hipLaunchKernelGGL(k_reduce_systems<64>, dim3(a.n_sys), dim3(64), 0, (hipStream_t)stream, a, moments,
+                           reset);
+    else
+        hipLaunchKernelGGL(k_reduce_systems<kSumBlock>, dim3(a.n_sys), dim3(kSumBlock), 0, (hipStream_t)stream,
+                           a, moments, reset);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
