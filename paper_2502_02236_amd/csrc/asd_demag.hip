@@ -250,8 +250,9 @@ __global__ __launch_bounds__(kDmThreads) void k_dm_gather_x(DemagDev dm, const T
 
 // --- 1': the same from given cell sums: src [S][3][ns][ncell] (cells x
 // fastest, in units of the spin sums of a coarse cell; ns partial sums per
-// cell, 1 when dm.ns is 0); FFT along x
-template <typename T, typename U>
+// cell, 1 when dm.ns is 0); FFT along x.  WHOLE: one sum per cell (read as eight
+// slots it took 22.4 us on the FP64 mesh of 252 x 50 x 11 cells, 21.1 so)
+template <typename T, typename U, bool WHOLE>
 __global__ __launch_bounds__(kDmThreads) void k_dm_cells_x(DemagDev dm, const U *__restrict__ src)
 {
     const int Px = 1 << dm.lx;
@@ -264,8 +265,8 @@ __global__ __launch_bounds__(kDmThreads) void k_dm_cells_x(DemagDev dm, const U 
         const int c = q / dm.ncx, i = q - c * dm.ncx;
         const U *p = src + ((int64_t)s * 3 + c) * ns * dm.ncell + cell0 + i;
         T v = T(0);
-        if (ns == 1) v = (T)p[0];  // sums that come whole (eight loads of the one: 22.4 us, 21.1 so)
-        for (int s0 = 0; ns > 1 && s0 < ns; s0 += 8) {
+        if constexpr (WHOLE) v = (T)p[0];
+        for (int s0 = 0; !WHOLE && s0 < ns; s0 += 8) {
             U t[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) t[u] = p[(int64_t)min(s0 + u, ns - 1) * dm.ncell];
@@ -614,8 +615,10 @@ int run_demag(const DemagDev &dm, const T *S, int64_t ncs, const SysDev *sys,
     const size_t cb = sizeof(Cx<T>);
     const dim3 blk(kDmThreads);
     const dim3 grows(dm.ncy * dm.ncz, dm.n_sys);
-    if (cells)
-        hipLaunchKernelGGL((k_dm_cells_x<T, U>), grows, blk, row_lds_bytes(Px, cb), st, dm, cells);
+    if (cells && dm.ns <= 1)
+        hipLaunchKernelGGL((k_dm_cells_x<T, U, true>), grows, blk, row_lds_bytes(Px, cb), st, dm, cells);
+    else if (cells)
+        hipLaunchKernelGGL((k_dm_cells_x<T, U, false>), grows, blk, row_lds_bytes(Px, cb), st, dm, cells);
     else
         hipLaunchKernelGGL(k_dm_gather_x<T>, grows, blk, row_lds_bytes(Px, cb), st, dm, S, ncs, sys,
                            origin);
