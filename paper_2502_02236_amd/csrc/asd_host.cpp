@@ -1481,8 +1481,10 @@ int asd_reduce_energy(asd_t *h, double *per_system)
         rc = launch_energy_f32(e, L.n_tiles, h->stream);
     }
     h->kernel = saved;
+    int max_tiles = 0;
+    for (const SysDev &d : h->dev) max_tiles = std::max(max_tiles, (int)d.n_tiles);
     if (rc || launch_energy_finish((const double *)(w + L.off_epart), (const SysDev *)(w + L.off_sys),
-                                   (int)h->sys.size(), (double *)(w + L.off_eout), h->stream))
+                                   (int)h->sys.size(), max_tiles, (double *)(w + L.off_eout), h->stream))
         return fail(h, ASD_EHIP, "energy launch failed");
     HIP_OK(h, hipMemcpyAsync(per_system, w + L.off_eout, h->sys.size() * 4 * sizeof(double),
                              hipMemcpyDeviceToHost, h->stream));

@@ -244,8 +244,8 @@ struct TransferArgs {
 int launch_coarse_grain(const TransferArgs &a, void *stream);
 int launch_cone_columns(const TransferArgs &a, void *stream);
 // sum the energy partials of each system's tiles in order -> [S][4]
-int launch_energy_finish(const double *partial, const SysDev *sys, int n_sys, double *sys_out,
-                         void *stream);
+int launch_energy_finish(const double *partial, const SysDev *sys, int n_sys, int max_tiles,
+                         double *sys_out, void *stream);
 int launch_energy_f64(const EnergyArgs<double> &a, int n_tiles, void *stream);
 int launch_energy_f32(const EnergyArgs<float> &a, int n_tiles, void *stream);
 // Metropolis sweeps in place on st.S (checkerboard colour 0, then 1); the

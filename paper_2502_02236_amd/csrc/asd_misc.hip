@@ -353,30 +353,52 @@ int launch_reduce_systems(const RedArgs &a, int moments, int reset, void *stream
 }
 
 // The tiles' partial energies of a system, one workgroup per system: thread
-// t adds tiles t, t + kSumBlock, ... in order, then the workgroup its threads
+// t adds tiles t, t + B, ... in order, then the workgroup its threads
 // in a fixed tree (the same FP64 result every run).  One thread walking the
 // tiles was a chain of dependent loads and adds: 1147 us for the 10 313 tiles
 // of a 400x200x33 window, 13 us this way.
-__global__ __launch_bounds__(kSumBlock) void k_energy_finish(const double *partial,
-                                                             const SysDev *sys, double *out)
+template <int B>
+__global__ __launch_bounds__(B) void k_energy_finish(const double *partial, const SysDev *sys, double *out)
 {
     const int s = blockIdx.x;
     const int b0 = sys[s].tile_base, b1 = b0 + sys[s].n_tiles;
     double t[3] = {0.0, 0.0, 0.0};
-    for (int b = b0 + (int)threadIdx.x; b < b1; b += kSumBlock)
+    for (int b = b0 + (int)threadIdx.x; b < b1; b += B)
         for (int k = 0; k < 3; ++k) t[k] += partial[3 * (int64_t)b + k];
-    block_sum<kSumBlock>(t);
+    block_sum<B>(t);
     if (threadIdx.x == 0) {
         for (int k = 0; k < 3; ++k) out[4 * (int64_t)s + k] = t[k];
         out[4 * (int64_t)s + 3] = (t[0] + t[1]) + t[2];
     }
 }
 
-int launch_energy_finish(const double *partial, const SysDev *sys, int n_sys, double *sys_out,
-                         void *stream)
+// a thread per system, batches of small systems: 4096 of 512 sites 91 us a call with a
+// workgroup of 1024 threads each, 69 with a wavefront each, 65 so
+__global__ __launch_bounds__(64) void k_energy_finish_few(const double *partial, const SysDev *sys,
+                                                          int n_sys, double *out)
 {
-    hipLaunchKernelGGL(k_energy_finish, dim3(n_sys), dim3(kSumBlock), 0, (hipStream_t)stream, partial,
-                       sys, sys_out);
+    const int s = blockIdx.x * blockDim.x + threadIdx.x;
+    if (s >= n_sys) return;
+    const int b0 = sys[s].tile_base, b1 = b0 + sys[s].n_tiles;
+    double t[3] = {0.0, 0.0, 0.0};
+    for (int b = b0; b < b1; ++b)
+        for (int k = 0; k < 3; ++k) t[k] += partial[3 * (int64_t)b + k];
+    for (int k = 0; k < 3; ++k) out[4 * (int64_t)s + k] = t[k];
+    out[4 * (int64_t)s + 3] = (t[0] + t[1]) + t[2];
+}
+
+int launch_energy_finish(const double *partial, const SysDev *sys, int n_sys, int max_tiles,
+                         double *sys_out, void *stream)
+{
+    if (max_tiles <= 8)
+        hipLaunchKernelGGL(k_energy_finish_few, dim3((n_sys + 63) / 64), dim3(64), 0, (hipStream_t)stream,
+                           partial, sys, n_sys, sys_out);
+    else if (max_tiles <= 64)  // one wavefront covers them: 512 systems of 2816 sites 50.5 -> 47.5 us a call
+        hipLaunchKernelGGL(k_energy_finish<64>, dim3(n_sys), dim3(64), 0, (hipStream_t)stream, partial, sys,
+                           sys_out);
+    else
+        hipLaunchKernelGGL(k_energy_finish<kSumBlock>, dim3(n_sys), dim3(kSumBlock), 0, (hipStream_t)stream,
+                           partial, sys, sys_out);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
