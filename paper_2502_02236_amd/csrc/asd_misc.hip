@@ -224,15 +224,15 @@ __device__ __forceinline__ bool site_in_window(const SysDev &d, int org, int32_t
 // Spin sums of the grains, each grain's site list (ascending site index) cut
 // into n_parts equal parts, one workgroup per part.  Each pass covers kRedUnroll
 // * kRedBlock sites: thread t takes sites t, t + kRedBlock, ... (coalesced),
-// loads them all, then adds them in that order; the workgroup then sums its
-// threads in a fixed tree.  The order depends only on the site list, so the
+// loads them all (beyond the part its last site, for a site outside the window the
+// system's first one: without branches between them all are in flight, 512 systems
+// of 2816 sites 9.0 -> 6.7 us), then adds them in that order; the workgroup then sums
+// its threads in a fixed tree.  The order depends only on the site list, so the
 // FP64 result is the same in every run.  Bound by the latency of the gather
 // (index, then spins): one workgroup per grain left most of the chip idle (40
 // us for the 224 grains of a 400x200x33 window, 50 us for 32 isolated grains).
 constexpr int kRedBlock = 256;
-// sites per thread and pass (independent loads): a part of up to 2048 sites in one
-// pass (64 systems of 2880 sites 18.2 us a moment sample, 19.6 in passes of four and
-// with k_reduce_systems in 1024 threads)
+// sites per thread and pass (independent loads): a part of up to 2048 sites in one pass
 constexpr int kRedUnroll = 8;
 
 template <typename T>
@@ -254,25 +254,24 @@ __global__ __launch_bounds__(kRedBlock) void k_reduce_parts(RedArgs a)
         for (int j = 0; j < kRedUnroll; ++j) {
             const int64_t k = base + threadIdx.x + (int64_t)j * kRedBlock;
             ok[j] = k < k1;
-            loc[j] = ok[j] ? a.grain_sites[k] : 0;
+            loc[j] = a.grain_sites[ok[j] ? k : k1 - 1];
         }
         T v[kRedUnroll][3];
 #pragma unroll
         for (int j = 0; j < kRedUnroll; ++j) {
             ok[j] = ok[j] && site_in_window(d, org, loc[j]);
-            const int64_t i = d.base + loc[j];
-            v[j][0] = ok[j] ? S[i] : T(0);
-            v[j][1] = ok[j] ? S[a.ncs + i] : T(0);
-            v[j][2] = ok[j] ? S[2 * a.ncs + i] : T(0);
+            const int64_t i = d.base + (ok[j] ? loc[j] : 0);
+            v[j][0] = S[i];
+            v[j][1] = S[a.ncs + i];
+            v[j][2] = S[2 * a.ncs + i];
         }
 #pragma unroll
-        for (int j = 0; j < kRedUnroll; ++j)
-            if (ok[j]) {
-                acc[0] += (double)v[j][0];
-                acc[1] += (double)v[j][1];
-                acc[2] += (double)v[j][2];
-                acc[3] += 1.0;
-            }
+        for (int j = 0; j < kRedUnroll; ++j) {
+            acc[0] += ok[j] ? (double)v[j][0] : 0.0;
+            acc[1] += ok[j] ? (double)v[j][1] : 0.0;
+            acc[2] += ok[j] ? (double)v[j][2] : 0.0;
+            acc[3] += ok[j] ? 1.0 : 0.0;
+        }
     }
     block_sum<kRedBlock>(acc);
     if (threadIdx.x == 0)
@@ -290,12 +289,30 @@ int launch_reduce_grains(const RedArgs &a, void *stream)
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
+// the sums t of system s; optional moment statistics of m = |M| / N: samples,
+// sum m, sum m^2, sum m^4
+__device__ __forceinline__ void system_out(const RedArgs &a, int s, const double (&t)[4], int moments,
+                                           int reset)
+{
+    for (int k = 0; k < 4; ++k) a.sys_out[4 * (int64_t)s + k] = t[k];
+    if (moments) {
+        double *mo = a.moments + 5 * (int64_t)s;
+        if (reset)
+            for (int k = 0; k < 5; ++k) mo[k] = 0.0;
+        double m = t[3] > 0.0 ? sqrt(t[0] * t[0] + t[1] * t[1] + t[2] * t[2]) / t[3] : 0.0;
+        double m2 = m * m;
+        mo[0] += 1.0;
+        mo[1] += m;
+        mo[2] += m2;
+        mo[3] += m2 * m2;
+    }
+}
+
 // One workgroup of B threads per system: every grain's sum from its parts in order
 // (a thread per grain up to kPartsThread parts, a wavefront per grain beyond),
-// then the system's from its grains in a fixed tree; optional moment
-// statistics of m = |M| / N: samples, sum m, sum m^2, sum m^4.  One thread
-// walking the 224 grains of a window took 28 us.  Systems whose grains one
-// wavefront covers get no more than that (the same sums: the others would add zeros).
+// then the system's from its grains in a fixed tree.  One thread walking the 224
+// grains of a window took 28 us.  Systems whose grains one wavefront covers get no
+// more than that (the same sums: the others would add zeros).
 constexpr int kPartsThread = 16;
 
 template <int B>
@@ -324,26 +341,35 @@ __global__ __launch_bounds__(B) void k_reduce_systems(RedArgs a, int moments, in
         }
     }
     block_sum<B>(t);
-    if (threadIdx.x != 0) return;
-    for (int k = 0; k < 4; ++k) a.sys_out[4 * (int64_t)s + k] = t[k];
-    if (moments) {
-        double *mo = a.moments + 5 * (int64_t)s;
-        if (reset)
-            for (int k = 0; k < 5; ++k) mo[k] = 0.0;
-        double m = t[3] > 0.0 ? sqrt(t[0] * t[0] + t[1] * t[1] + t[2] * t[2]) / t[3] : 0.0;
-        double m2 = m * m;
-        mo[0] += 1.0;
-        mo[1] += m;
-        mo[2] += m2;
-        mo[3] += m2 * m2;
+    if (threadIdx.x == 0) system_out(a, s, t, moments, reset);
+}
+
+// a thread per system: batches of isolated grains (one grain each, of few parts).  A
+// moment sample of 64 systems of 2816 sites takes 16.8 us with it, 4096 of 512 sites
+// 30.6 (19.2 and 34.5 with a wavefront per system and branches between the loads)
+__global__ __launch_bounds__(64) void k_reduce_isolated(RedArgs a, int moments, int reset)
+{
+    const int s = blockIdx.x * blockDim.x + threadIdx.x;
+    if (s >= a.n_sys) return;
+    double t[4] = {0.0, 0.0, 0.0, 0.0};
+    if (a.sys[s].n_grains > 0) {
+        const int64_t g = a.sys[s].grain_base;
+        const double *p = a.part + 4 * g * a.n_parts;
+        for (int q = 0; q < a.n_parts; ++q)
+            for (int k = 0; k < 4; ++k) t[k] += p[4 * q + k];
+        for (int k = 0; k < 4; ++k) a.grain_out[4 * g + k] = t[k];
     }
+    system_out(a, s, t, moments, reset);
 }
 
 int launch_reduce_systems(const RedArgs &a, int moments, int reset, void *stream)
 {
     if (a.n_sys == 0) return 0;
     const int threads = a.n_parts > kPartsThread ? 64 * a.max_grains : a.max_grains;
-    if (threads <= 64)
+    if (a.max_grains <= 1 && a.n_parts <= kPartsThread)
+        hipLaunchKernelGGL(k_reduce_isolated, dim3((a.n_sys + 63) / 64), dim3(64), 0, (hipStream_t)stream, a,
+                           moments, reset);
+    else if (threads <= 64)
         hipLaunchKernelGGL(k_reduce_systems<64>, dim3(a.n_sys), dim3(64), 0, (hipStream_t)stream, a, moments,
                            reset);
     else
