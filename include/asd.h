@@ -215,7 +215,8 @@ int asd_reduce_magnetization(asd_t *h, double *per_grain, double *per_system);
  * (serving loops, code between graph captures, harnesses that forbid
  * hipMalloc): the per-grain and per-system sums are kept in a static
  * device array of the library (1 MiB on each device it runs on, held
- * until the process ends) instead of the handle's workspace; nothing is
+ * until the process ends) instead of the handle's workspace, which holds
+ * only the sums of the parts that long grains are added in; nothing is
  * allocated.  Same arguments, kernels, summation order and results as
  * asd_reduce_magnetization.  Limit: n_grains + n_systems <= 32768 over the
  * handle, else ASD_EINVAL before anything is enqueued.  Either pointer may

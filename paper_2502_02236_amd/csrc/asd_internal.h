@@ -67,10 +67,10 @@ struct DemagDev {
     int32_t ncell;            // ncx * ncy * ncz
     int32_t lx, ly, lz;       // log2 of the padded sizes Px, Py, Pz
     int32_t xb_y, xb_z;       // x lines per workgroup in the y and z passes
-    int32_t yzf;              // 1: the y and z passes as one workgroup per (kx,
-                              // system) with direct sums along z (ncz <= 16), K
-                              // the tensor transformed along x and y only
-                              // (demag_mixed)
+    int32_t yzf;              // 1: the y and z passes in one kernel, a workgroup per
+                              // (kx, system) or three where they all fit the chip
+                              // at once, with direct sums along z (ncz <= 16), K the
+                              // tensor transformed along x and y only (demag_mixed)
     int32_t n_sys;
     FastDivH fd_cx, fd_cy, fd_cz;
     // stray field of a frozen track: the same pipeline on a mesh that

@@ -15,9 +15,12 @@
 // [0, 1] in FP64 for both precisions.  T per cell from the laser spot at
 // the stage time t_n, t_n + dt/2, t_n + dt/2, t_n + dt.
 //
-// One launch per RK4 stage; stage inputs ping-pong between two buffers so
-// that no launch overwrites what its neighbours read; the last stage writes
-// the new magnetisation in place (each cell reads only its own old value).
+// A spot that does not move: the whole step in one launch on tiles held in LDS
+// where the mesh's sizes call for it (mm_pick_tile), the new magnetisation written
+// to a second buffer that takes the first one's place.  Otherwise one launch per
+// RK4 stage: stage inputs ping-pong between two buffers so that no launch
+// overwrites what its neighbours read, and the last stage writes the new
+// magnetisation in place (each cell reads only its own old value).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -1289,7 +1292,7 @@ static int multiscale_run(asd_t *atoms, int32_t sys, asd_mm_t *left, asd_mm_t *r
         if (m && (rc = region_fits(m, dt, edge, cell, ny, nz, st))) return rc;
     if (nx < cx || org < cx) return mm_fail(nullptr, ASD_EINVAL, "window too narrow or too close to the track start");
     // both regions in the same precision under a spot that does not move: one
-    // launch per RK4 stage for the two
+    // launch for the two (one per RK4 stage where mm_step_pair takes the stages)
     const bool pair = left && right && left->elem == right->elem &&
                       left->drive.spot_mode != ASD_SPOT_MOVING &&
                       right->drive.spot_mode != ASD_SPOT_MOVING;
