@@ -94,15 +94,21 @@ struct FusedModel {
     // regions' steps, whose launches leave the caches cold, by 13 %, FP32 L1_0 130 x
     // 156 x 27 by 1 %)
     double margin;
+    // factor on tiles of eight wavefronts: in FP64 they came out 9 to 22 % above the
+    // model beside the first of the list (32 lattices), and with the margin alone some
+    // were slower than it (two systems of 304 x 92 x 44 sites 107 -> 112 us, 16 of 32 x
+    // 32 x 32 52.5 -> 54.2) or than four wavefronts without chunks (35 of 160 x 93 x 39
+    // 788, 708 so); with the factor the pick is at most 1 % slower than the first on 61
+    double eight;
 };
 
 inline FusedModel fused_model(bool l10, bool fp64)
 {
     if (l10)
-        return fp64 ? FusedModel{2.2, 1.507, 1.507, 5.85, 0.0, 1, 1, 0.9}
-                    : FusedModel{3.3, 0.133, 0.133, 0.4, 2.32, 3, 3, 0.9};
-    return fp64 ? FusedModel{3.8, 0.25, 0.25, 0.85, 1.0, 2, 2, 0.9}
-                : FusedModel{3.5, 0.086, 0.061, 0.35, 0.345, 3, 4, 0.85};
+        return fp64 ? FusedModel{2.2, 1.507, 1.507, 5.85, 0.0, 1, 1, 0.9, 1.0}
+                    : FusedModel{3.3, 0.133, 0.133, 0.4, 2.32, 3, 3, 0.9, 1.0};
+    return fp64 ? FusedModel{3.8, 0.25, 0.25, 0.85, 1.0, 2, 2, 0.9, 1.07}
+                : FusedModel{3.5, 0.086, 0.061, 0.35, 0.345, 3, 4, 0.85, 1.0};
 }
 
 inline double fused_model_us(const FusedModel &m, const FusedVariant &f, double n, double planes_all,
@@ -117,7 +123,8 @@ inline double fused_model_us(const FusedModel &m, const FusedVariant &f, double 
         return planes * ((t > m.chain ? t : m.chain) + m.latency);
     };
     const int64_t slots = 256 * (int64_t)per_cu, full = (int64_t)n / slots, rest = (int64_t)n - full * slots;
-    return m.launch + full * round(per_cu) + (rest > 0 ? round((double)((rest + 255) / 256)) : 0.0);
+    const double t = m.launch + full * round(per_cu) + (rest > 0 ? round((double)((rest + 255) / 256)) : 0.0);
+    return f.waves == 8 ? t * m.eight : t;
 }
 
 // the variants fused_default chooses from (one column per lane), the first of the
