@@ -396,8 +396,8 @@ __global__ __launch_bounds__(kDmThreads) void k_dm_z(DemagDev dm)
 // sums and of the inverse ones, has its row of the tensor in LDS before the sums
 // ask for it, and writes to wy, since its neighbours still read wx.  All loads of
 // the column and the tensor are issued together; a whole column in one workgroup
-// keeps the plain loop (FP64, 11 planes of 512 x 128 points: 67.7 us before the
-// split, 72.3 with the batched loads, 70.5 so).  Lanes: four groups of
+// keeps the plain loop (11 planes: FP64, 257 columns of 128 rows 68.1 us before the
+// split, 68.6 so; FP32, 2064 columns 101.9 and 101.2).  Lanes: four groups of
 // Py, group q computing the planes q, q + 4, ... (wavefront-uniform, so the
 // unrolled sums need no divergent branches).
 constexpr int kDmYzThreads = 512;
@@ -447,9 +447,31 @@ __device__ __forceinline__ int yz_comp(int c, int e)
     return c == e ? c : c + e + 2;
 }
 
-// output component C (all three: -1) of one ky, the planes Q0, Q0 + 4, ...; tensor
-// component comp at d oy of k(comp); xy and yz odd in ky, xz and yz imaginary and odd
-// in dz.  A single component goes to the first NCZ lines of o.
+// the three output components of one ky, the planes Q0, Q0 + 4, ... (tensor at
+// kt + (comp NCZ + d) oy; xy and yz odd in ky, xz and yz imaginary and odd in dz).  Of
+// its own beside yz_column: through that one's tensor argument it spilled 32 vector
+// registers instead of 12 (FP32, 11 planes), 2064 columns 101 -> 108 us.
+template <typename T, int NCZ, int Q0>
+__device__ __forceinline__ void yz_whole(const T *__restrict__ kt, int oy, T sy,
+                                         const Cx<T> *__restrict__ r, Cx<T> *__restrict__ o,
+                                         int ls, int ky)
+{
+    // the sources of this ky (3 NCZ values) once
+    Cx<T> m[3][NCZ];
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int zs = 0; zs < NCZ; ++zs) m[c][zs] = r[(c * NCZ + zs) * ls + ky];
+    const int64_t cs = (int64_t)NCZ * oy;  // component stride
+    const T *kxx = kt, *kyy = kt + cs, *kzz = kt + 2 * cs, *kxy = kt + 3 * cs, *kxz = kt + 4 * cs,
+            *kyz = kt + 5 * cs;
+    yz_row<T, NCZ, Q0, false, false, true>(kxx, kxy, kxz, T(1), sy, T(1), oy, m, o, ls, ky, 0);
+    yz_row<T, NCZ, Q0, false, false, true>(kxy, kyy, kyz, sy, T(1), sy, oy, m, o, ls, ky, 1);
+    yz_row<T, NCZ, Q0, true, true, false>(kxz, kyz, kzz, T(1), sy, T(1), oy, m, o, ls, ky, 2);
+}
+
+// the same for output component C alone, to the first NCZ lines of o; tensor
+// component comp at d oy of k(comp)
 template <typename T, int NCZ, int Q0, int C, class K>
 __device__ __forceinline__ void yz_column(const K &k, int oy, T sy, const Cx<T> *__restrict__ r,
                                           Cx<T> *__restrict__ o, int ls, int ky)
@@ -460,12 +482,12 @@ __device__ __forceinline__ void yz_column(const K &k, int oy, T sy, const Cx<T> 
     for (int c = 0; c < 3; ++c)
 #pragma unroll
         for (int zs = 0; zs < NCZ; ++zs) m[c][zs] = r[(c * NCZ + zs) * ls + ky];
-    if (C == 0 || C < 0)
+    if (C == 0)
         yz_row<T, NCZ, Q0, false, false, true>(k(0), k(3), k(4), T(1), sy, T(1), oy, m, o, ls, ky, 0);
-    if (C == 1 || C < 0)
-        yz_row<T, NCZ, Q0, false, false, true>(k(3), k(1), k(5), sy, T(1), sy, oy, m, o, ls, ky, C < 0 ? 1 : 0);
-    if (C == 2 || C < 0)
-        yz_row<T, NCZ, Q0, true, true, false>(k(4), k(5), k(2), T(1), sy, T(1), oy, m, o, ls, ky, C < 0 ? 2 : 0);
+    if (C == 1)
+        yz_row<T, NCZ, Q0, false, false, true>(k(3), k(1), k(5), sy, T(1), sy, oy, m, o, ls, ky, 0);
+    if (C == 2)
+        yz_row<T, NCZ, Q0, true, true, false>(k(4), k(5), k(2), T(1), sy, T(1), oy, m, o, ls, ky, 0);
 }
 
 template <typename T, int NCZ, int C, class K>
@@ -551,8 +573,12 @@ __global__ __launch_bounds__(kDmYzThreads, sizeof(T) == 4 && NCZ <= 11 ? 4 : 2) 
             else
                 yz_group<T, NCZ, 2>(q, k2, oy, sy, r, o, ls, ky);
         } else {
-            auto k = [&](int p) { return kt + (int64_t)p * NCZ * oy + kyr; };
-            yz_group<T, NCZ, -1>(q, k, oy, sy, r, o, ls, ky);
+            switch (q) {
+            case 0: yz_whole<T, NCZ, 0>(kt + kyr, oy, sy, r, o, ls, ky); break;
+            case 1: yz_whole<T, NCZ, 1>(kt + kyr, oy, sy, r, o, ls, ky); break;
+            case 2: yz_whole<T, NCZ, 2>(kt + kyr, oy, sy, r, o, ls, ky); break;
+            default: yz_whole<T, NCZ, 3>(kt + kyr, oy, sy, r, o, ls, ky); break;
+            }
         }
     }
     __syncthreads();
